@@ -158,7 +158,7 @@ constexpr long long partial_rows(long long n, int ipl) {
   const long long by_items = n + it_max + (long long)kSliceItems * it_max;
   const long long by_slices = ((n + kMinSlice - 1) / kMinSlice) * n;
   const long long rows = by_items < by_slices ? by_items : by_slices;
-  // Also scratch of the diagnostics sort: 1.5 * 2n + n / 64 + 8 doubles.
+  // Also scratch of the diagnostics (of 6 rows doubles): 4 n + n / 64 + 5 of them.
   return rows > n + 16 ? rows : n + 16;
 }
 

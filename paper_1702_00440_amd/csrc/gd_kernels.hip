@@ -1851,10 +1851,17 @@ __global__ void k_pool_status(const PoolSlot* __restrict__ slots, const PoolTabl
 //
 // Lagrange radius of mass fraction f: about the centre of mass, the distance
 // of the first particle (in ascending distance, ties by index) at which the
-// cumulative mass reaches f times the total. The distances are sorted on the
-// device (bitonic network over the bit patterns of r^2, which order like the
-// values for r^2 >= 0) and the masses are accumulated in sorted order by one
-// lane, so the cumulative sums are the plain sequential ones.
+// cumulative mass reaches f times the total, both summed one after the other.
+//
+// What bounds it: the launches and the wait for the result. The sort keys are
+// the bit patterns of r^2 (which order like the values for r^2 >= 0). Runs of
+// kDiagRun keys are sorted in LDS, one workgroup each, and 16 runs at a time
+// are merged in one launch: an element's place is its index in its own run
+// plus, from a binary search in each other run, the elements before it. The
+// cumulative masses are then prefix sums of one workgroup (k_diag_scan).
+// Measured at N = 16384: 5557 us a call with a bitonic network of 105 launches
+// in global memory and a scan by one lane (dependent loads, 4.3 ms of it),
+// 90 us now.
 
 struct DiagArgs {
   int n_frac;
@@ -1888,81 +1895,279 @@ __global__ __launch_bounds__(kBlock) void k_diag_com(int n, const double* __rest
     for (int q = 0; q < 4; ++q) wg_out[4 * blockIdx.x + q] = red[q][0];
 }
 
-// Sort keys: bit pattern of r^2 about the centre of mass (padding: max key).
-__global__ __launch_bounds__(kBlock) void k_diag_keys(int n, int npow2, int nwg,
-                                                      const double* __restrict__ wg,
-                                                      const double* __restrict__ x,
-                                                      const double* __restrict__ y,
-                                                      const double* __restrict__ z,
-                                                      unsigned long long* __restrict__ key,
-                                                      int* __restrict__ idx) {
-  __shared__ double com[4];
+constexpr int kDiagRun = 1024;      // keys of one run sorted in LDS
+constexpr int kDiagSortBlock = 512;  // its threads: one compare-exchange each per stage
+constexpr int kDiagWays = 16;        // runs merged by one launch
+constexpr int kDiagScanBlock = 1024;
+
+// The sums of the workgroups of k_diag_com added one after the other
+// (total[0..3]: m, m x, m y, m z), staged through LDS (stage: 4 * kDiagRun
+// doubles). Every thread of the workgroup calls it.
+__device__ __forceinline__ void diag_totals(const double* __restrict__ wg, int nwg, double* stage,
+                                            double (&total)[4]) {
   const int tid = threadIdx.x;
-  if (tid < 4) {
-    double acc = 0.0;
-    for (int b = 0; b < nwg; ++b) acc += wg[4 * b + tid];
-    com[tid] = acc;
+  double acc = 0.0;
+  for (int b0 = 0; b0 < nwg; b0 += kDiagRun) {
+    const int nb = min(kDiagRun, nwg - b0);
+    for (int k = tid; k < 4 * nb; k += blockDim.x) stage[k] = wg[4 * (size_t)b0 + k];
+    __syncthreads();
+    if (tid < 4)
+      for (int b = 0; b < nb; ++b) acc += stage[4 * b + tid];
+    __syncthreads();
   }
+  if (tid < 4) stage[tid] = acc;
   __syncthreads();
-  const int i = blockIdx.x * kBlock + tid;
-  if (i >= npow2) return;
-  if (i < n) {
-    const double dx = x[i] - com[1] / com[0], dy = y[i] - com[2] / com[0], dz = z[i] - com[3] / com[0];
-    const double r2 = dx * dx + dy * dy + dz * dz;
-    key[i] = (unsigned long long)__double_as_longlong(r2);
-  } else {
-    key[i] = ~0ULL;
-  }
-  idx[i] = i;
+  for (int q = 0; q < 4; ++q) total[q] = stage[q];
+  __syncthreads();
 }
 
-// One compare-exchange stage of the bitonic network on (key, index) pairs.
-__global__ __launch_bounds__(kBlock) void k_bitonic(int npow2, int j, int k,
-                                                    unsigned long long* __restrict__ key,
-                                                    int* __restrict__ idx) {
+// Sort keys (the bit pattern of r^2 about the centre of mass) of the run
+// [kDiagRun * blockIdx.x, ...), sorted by (key, index) in LDS. A run past the
+// end is filled with the largest key and the indices that follow, which sort
+// last.
+__global__ __launch_bounds__(kDiagSortBlock) void k_diag_sort(int n, int nwg, const double* __restrict__ wg,
+                                                              const double* __restrict__ x,
+                                                              const double* __restrict__ y,
+                                                              const double* __restrict__ z,
+                                                              unsigned long long* __restrict__ key,
+                                                              int* __restrict__ idx) {
+  __shared__ union {
+    double stage[4 * kDiagRun];
+    struct {
+      unsigned long long k[kDiagRun];
+      int i[kDiagRun];
+    } run;
+  } u;
+  const int tid = threadIdx.x;
+  double com[4];
+  diag_totals(wg, nwg, u.stage, com);
+  const int base = blockIdx.x * kDiagRun;
+  for (int e = tid; e < kDiagRun; e += kDiagSortBlock) {
+    const int i = base + e;
+    unsigned long long kk = ~0ULL;
+    if (i < n) {
+      const double dx = x[i] - com[1] / com[0], dy = y[i] - com[2] / com[0], dz = z[i] - com[3] / com[0];
+      kk = (unsigned long long)__double_as_longlong(dx * dx + dy * dy + dz * dz);
+    }
+    u.run.k[e] = kk;
+    u.run.i[e] = i;
+  }
+  for (int k = 2; k <= kDiagRun; k <<= 1)
+    for (int j = k >> 1; j > 0; j >>= 1) {
+      __syncthreads();
+      // pair (a, a + j) number tid: a has bit j clear
+      const int a = 2 * (tid & ~(j - 1)) + (tid & (j - 1)), b = a + j;
+      const unsigned long long ka = u.run.k[a], kb = u.run.k[b];
+      const int ia = u.run.i[a], ib = u.run.i[b];
+      const bool greater = ka > kb || (ka == kb && ia > ib);
+      if (greater == ((a & k) == 0)) {
+        u.run.k[a] = kb; u.run.k[b] = ka;
+        u.run.i[a] = ib; u.run.i[b] = ia;
+      }
+    }
+  __syncthreads();
+  for (int e = tid; e < kDiagRun; e += kDiagSortBlock)
+    if (base + e < n) {
+      key[base + e] = u.run.k[e];
+      idx[base + e] = u.run.i[e];
+    }
+}
+
+// One merge pass: groups of kDiagWays sorted runs of len keys each become one
+// sorted run. Runs hold ascending ranges of indices, so elements of an earlier
+// run come first among equal keys.
+__global__ __launch_bounds__(kBlock) void k_diag_merge(int n, long long len,
+                                                       const unsigned long long* __restrict__ key,
+                                                       const int* __restrict__ idx,
+                                                       unsigned long long* __restrict__ key_out,
+                                                       int* __restrict__ idx_out) {
   const int i = blockIdx.x * kBlock + threadIdx.x;
-  if (i >= npow2) return;
-  const int l = i ^ j;
-  if (l <= i) return;
-  const bool up = (i & k) == 0;
-  const unsigned long long ki = key[i], kl = key[l];
-  const int ii = idx[i], il = idx[l];
-  const bool greater = ki > kl || (ki == kl && ii > il);
-  if (greater == up) {
-    key[i] = kl;
-    key[l] = ki;
-    idx[i] = il;
-    idx[l] = ii;
-  }
-}
-
-// One lane: total mass in index order, cumulative mass in sorted order, the
-// radius for each fraction, and Eq. (5) for the half-mass radius
-// (out[n_frac]; out[n_frac + 1] is the radius at f = 1/2).
-__global__ void k_diag_scan(int n, const double* __restrict__ m,
-                            const unsigned long long* __restrict__ key, const int* __restrict__ idx,
-                            DiagArgs a, double* __restrict__ out) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
-  double mt = 0.0;
-  for (int i = 0; i < n; ++i) mt += m[i];
-  double cum = 0.0;
-  int f = 0;
-  double rh = 0.0;
-  bool rh_set = false;
-  for (int r = 0; r < n && (f < a.n_frac || !rh_set); ++r) {
-    cum += m[idx[r]];
-    const double rad = sqrt(__longlong_as_double((long long)key[r]));
-    while (f < a.n_frac && cum >= a.frac[f] * mt) out[f++] = rad;
-    if (!rh_set && cum >= 0.5 * mt) {
-      rh = rad;
-      rh_set = true;
+  if (i >= n) return;
+  const unsigned long long k = key[i];
+  const long long group = i / (len * kDiagWays) * (len * kDiagWays);
+  const int own = (int)((i - group) / len);
+  // The elements of run r before (k, i): keys <= k of an earlier run, < k of
+  // a later one. All searches go down together, so that each step waits for
+  // one round trip (run by run: 27.6 us at N = 16384, 19.6 us this way).
+  int before[kDiagWays];
+#pragma unroll
+  for (int r = 0; r < kDiagWays; ++r) before[r] = 0;
+  for (int step = (int)len; step > 0; step >>= 1) {
+    unsigned long long v[kDiagWays];
+#pragma unroll
+    for (int r = 0; r < kDiagWays; ++r)
+      v[r] = key[min(group + r * len + before[r] + step, (long long)n) - 1];
+#pragma unroll
+    for (int r = 0; r < kDiagWays; ++r) {
+      const int at = before[r] + step;  // whether that many precede: the last of them does
+      const bool in = at <= len && group + r * len + at <= n;
+      if (in && (v[r] < k || (v[r] == k && r < own))) before[r] = at;
     }
   }
-  const double last = sqrt(__longlong_as_double((long long)key[n - 1]));
-  while (f < a.n_frac) out[f++] = last;
-  if (!rh_set) rh = last;
-  out[a.n_frac + 1] = rh;
-  out[a.n_frac] = 0.138 * sqrt((double)n * rh * rh * rh / (mt / n)) / log(0.1 * n);
+  long long rank = i - group - own * len;
+#pragma unroll
+  for (int r = 0; r < kDiagWays; ++r) rank += r == own ? 0 : before[r];
+  key_out[group + rank] = k;
+  idx_out[group + rank] = idx[i];
+}
+
+// Inclusive prefix sum over the workgroup (kDiagScanBlock threads) of v, and
+// the total. part: one double per wave.
+__device__ __forceinline__ double diag_block_scan(double v, double* part, double& total) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  for (int d = 1; d < 64; d *= 2) {
+    const double o = __shfl_up(v, d, 64);
+    if (lane >= d) v += o;
+  }
+  if (lane == 63) part[wave] = v;
+  __syncthreads();
+  double before = 0.0;
+  total = 0.0;
+  for (int w = 0; w < kDiagScanBlock / 64; ++w) {
+    if (w == wave) before = total;
+    total += part[w];
+  }
+  __syncthreads();
+  return before + v;
+}
+
+// One workgroup: the radius for each fraction, Eq. (5) for the half-mass
+// radius (out[n_frac]) and that radius (out[n_frac + 1]).
+//
+// The definition is in sums taken one after the other (total mass in index
+// order, cumulative mass in sorted order), a serial chain. Prefix sums of the
+// whole workgroup decide the same wherever they can: any order of adding n
+// masses >= 0 is off by at most (n - 1) 2^-53 of the total, so a threshold
+// further than delta from the cumulative masses on both its sides is crossed
+// at the same particle; and when every mass is a multiple of the spacing of
+// doubles at the total (equal masses 1 / 2^k), all orders are exact. A
+// threshold that neither settles (equal masses 1 / 1000 at f = 1/2) takes the
+// serial chains: one lane per chain, from LDS. Measured: 23 us at N = 16384
+// (prefix sums), 600 us at N = 50000 with equal masses (the chains, 12 ns a
+// particle).
+__global__ __launch_bounds__(kDiagScanBlock) void k_diag_scan(int n, int nwg, const double* __restrict__ wg,
+                                                              const double* __restrict__ m,
+                                                              const unsigned long long* __restrict__ key,
+                                                              const int* __restrict__ idx, DiagArgs a,
+                                                              double* __restrict__ cum,
+                                                              double* __restrict__ out) {
+  constexpr int kChain = 2 * kDiagRun;  // masses of each chain staged at a time
+  __shared__ double stage[2 * kChain];
+  __shared__ double part[kDiagScanBlock / 64];
+  __shared__ int found[kMaxDiagFractions + 1];
+  __shared__ int unsure;
+  const int tid = threadIdx.x;
+  const int nf = a.n_frac + 1;  // the thresholds, with f = 1/2 last
+  double tot[4];
+  diag_totals(wg, nwg, stage, tot);
+  double mt = tot[0];
+  const double delta = (2.0 * n + 256.0) * 0x1p-53 * mt;
+  // spacing of doubles at twice the total: multiples of it add exactly
+  int e;
+  (void)frexp(2.0 * mt, &e);
+  int rest = mt > 0.0 ? 0 : 1;  // (no early exit: the loads stay independent)
+#pragma unroll 4
+  for (int i = tid; i < n; i += kDiagScanBlock) {
+    const double mi = m[i], s = ldexp(mi, 53 - e);
+    rest |= (s != rint(s)) | ((s == 0.0) & (mi != 0.0));
+  }
+  const bool exact = !__syncthreads_or(rest);
+  if (tid < nf) found[tid] = -1;
+  if (tid == 0) unsure = 0;
+  __syncthreads();
+  constexpr int kPer = 4;  // consecutive particles per thread
+  double carry = 0.0;
+  for (int b = 0; b < n; b += kDiagScanBlock * kPer) {
+    const int r0 = b + tid * kPer;
+    int id[kPer];
+    double c[kPer];
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) id[q] = idx[min(r0 + q, n - 1)];
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) c[q] = r0 + q < n ? m[id[q]] : 0.0;
+#pragma unroll
+    for (int q = 1; q < kPer; ++q) c[q] += c[q - 1];
+    double total;
+    const double incl = diag_block_scan(c[kPer - 1], part, total);
+    const double up = __shfl_up(incl, 1, 64);
+    if ((tid & 63) == 63) part[tid >> 6] = incl;
+    __syncthreads();
+    const double lo = carry + ((tid & 63) ? up : tid ? part[(tid >> 6) - 1] : 0.0);
+    const double hi = carry + incl;
+    __syncthreads();
+    carry += total;
+    for (int f = 0; f < nf; ++f) {
+      const double t = (f < a.n_frac ? a.frac[f] : 0.5) * mt;
+      if (!(lo < t && t <= hi)) continue;
+      // (the thread's last sum is the one that the next thread starts from)
+      double prev = lo;
+      for (int q = 0; q < kPer; ++q) {
+        const double next = q == kPer - 1 ? hi : lo + c[q];
+        if (prev < t && t <= next && r0 + q < n) {
+          found[f] = r0 + q;
+          if (!exact && (t - prev <= delta || next - t <= delta)) unsure = 1;
+        }
+        prev = next;
+      }
+    }
+  }
+  __syncthreads();
+  if (tid < nf && found[tid] < 0) unsure = 1;
+  __syncthreads();
+  if (unsure) {
+    // thread 0: total mass in index order; thread 64: cumulative mass
+    double acc = 0.0;
+    for (int b = 0; b < n; b += kChain) {
+      const int cnt = min(kChain, n - b);
+      for (int k = tid; k < kChain; k += kDiagScanBlock) {
+        stage[k] = k < cnt ? m[b + k] : 0.0;
+        stage[kChain + k] = k < cnt ? m[idx[b + k]] : 0.0;
+      }
+      __syncthreads();
+      // (32 masses per round trip to LDS; the tail of a stage is zeros, and
+      // sums past the end are not used)
+      if (tid == 0 || tid == 64) {
+        double* const st = stage + (tid ? kChain : 0);
+        for (int k = 0; k < cnt; k += 32) {
+          double v[32];
+#pragma unroll
+          for (int q = 0; q < 32; ++q) v[q] = st[k + q];
+#pragma unroll
+          for (int q = 0; q < 32; ++q) v[q] = acc += v[q];
+#pragma unroll
+          for (int q = 0; q < 32; ++q) st[k + q] = v[q];
+        }
+      }
+      __syncthreads();
+      for (int k = tid; k < cnt; k += kDiagScanBlock) cum[b + k] = stage[kChain + k];
+      __syncthreads();
+    }
+    if (tid == 0) stage[0] = acc;
+    __syncthreads();
+    mt = stage[0];
+    if (tid < nf) {
+      // the first particle at which the cumulative mass reaches the threshold
+      // (the last one if none does)
+      const double t = (tid < a.n_frac ? a.frac[tid] : 0.5) * mt;
+      int lo = 0, hi = n - 1;
+      while (lo < hi) {
+        const int mid = (lo + hi) >> 1;
+        if (cum[mid] >= t) hi = mid;
+        else lo = mid + 1;
+      }
+      found[tid] = lo;
+    }
+  }
+  __syncthreads();
+  if (tid < nf) {
+    const double rad = sqrt(__longlong_as_double((long long)key[found[tid]]));
+    if (tid < a.n_frac) {
+      out[tid] = rad;
+    } else {
+      out[a.n_frac + 1] = rad;
+      out[a.n_frac] = 0.138 * sqrt((double)n * rad * rad * rad / (mt / n)) / log(0.1 * n);
+    }
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -2129,29 +2334,33 @@ hipError_t launch_set_state(const Dev& d, const Consts& c, const double* x, cons
 hipError_t launch_diagnostics(const Dev& d, const Consts& c, const double* frac, int n_frac,
                               double* out, hipStream_t s) {
   const int n = c.n;
-  int npow2 = 1;
-  while (npow2 < n) npow2 <<= 1;
   const int nwg = grid_for(n);
   // Scratch in the partial-force buffer (unused between block steps): the
-  // workgroup sums, then keys and indices.
+  // workgroup sums, two sets of keys and indices, the cumulative masses.
   double* wg = d.part;
-  unsigned long long* key = (unsigned long long*)(d.part + 4 * (size_t)nwg + 8);
-  int* idx = (int*)(key + npow2);
+  unsigned long long* key[2];
+  key[0] = (unsigned long long*)(wg + 4 * (size_t)nwg);
+  key[1] = key[0] + n;
+  double* cum = (double*)(key[1] + n);
+  int* idx[2];
+  idx[0] = (int*)(cum + n);
+  idx[1] = idx[0] + n;
   hipLaunchKernelGGL(k_diag_com, dim3(nwg), dim3(kBlock), 0, s, n, d.m, d.x, d.y, d.z, wg);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_diag_keys, dim3(grid_for(npow2)), dim3(kBlock), 0, s, n, npow2, nwg, wg, d.x,
-                     d.y, d.z, key, idx);
+  hipLaunchKernelGGL(k_diag_sort, dim3((n + kDiagRun - 1) / kDiagRun), dim3(kDiagSortBlock), 0, s, n, nwg, wg,
+                     d.x, d.y, d.z, key[0], idx[0]);
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  for (int k = 2; k <= npow2; k <<= 1)
-    for (int j = k >> 1; j > 0; j >>= 1) {
-      hipLaunchKernelGGL(k_bitonic, dim3(grid_for(npow2)), dim3(kBlock), 0, s, npow2, j, k, key, idx);
-      if ((e = hipGetLastError()) != hipSuccess) return e;
-    }
+  int q = 0;
+  for (long long len = kDiagRun; len < n; len *= kDiagWays, q ^= 1) {
+    hipLaunchKernelGGL(k_diag_merge, dim3(nwg), dim3(kBlock), 0, s, n, len, key[q], idx[q], key[q ^ 1], idx[q ^ 1]);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+  }
   DiagArgs a{};
   a.n_frac = n_frac;
-  for (int q = 0; q < n_frac; ++q) a.frac[q] = frac[q];
-  hipLaunchKernelGGL(k_diag_scan, dim3(1), dim3(64), 0, s, n, d.m, key, idx, a, out);
+  for (int k = 0; k < n_frac; ++k) a.frac[k] = frac[k];
+  hipLaunchKernelGGL(k_diag_scan, dim3(1), dim3(kDiagScanBlock), 0, s, n, nwg, wg, d.m, key[q], idx[q], a, cum,
+                     out);
   return hipGetLastError();
 }
 
