@@ -28,6 +28,7 @@ using namespace gd;
 namespace {
 
 constexpr int kGraphSteps = 64;  // block steps per captured graph
+constexpr int kTeamRounds = 16;  // per captured graph of a context with a team: a team launch and a block step
 constexpr int kSchedWords = (int)((sizeof(Sched) + 7) / 8);  // 8-byte words of a status copy
 // Force-timing buckets by N_act: lower edges (the last bucket is open).
 constexpr int kProfBuckets = GD_PROFILE_BUCKETS;
@@ -48,7 +49,7 @@ size_t align_up(size_t v) { return (v + 255) & ~(size_t)255; }
 // Byte offsets of every array in the workspace.
 struct Layout {
   size_t sc, m, jm, x[3], v[3], a[3], j[3], p[3], pv[3], tick, lev, active, ip[3], ipv[3], ia[3], ij[3], ilev,
-      tag, part, ebuf, nact_log, total;
+      tag, part, ebuf, nact_log, xch, total;
 };
 
 // i particles per lane of a context's force kernel (see kIPerLaneLarge).
@@ -91,6 +92,10 @@ Layout make_layout(long long n, int ipl) {
   const long long eitems = std::max<long long>(make_eplan((int)n).items, kEnergyGrid);
   L.ebuf = take(sizeof(double) * 3 * (size_t)(eitems + 1));
   L.nact_log = take(sizeof(int) * 72);
+  // (contexts of a size that has teams hold kIPerLane i per lane; a pool's
+  // team of the same cluster has fewer owners and groups)
+  const Team t = make_team((int)n, kIPerLane, (int)n, false);
+  L.xch = take(t.wgs ? team_line_bytes(t) : 0);
   L.total = off;
   return L;
 }
@@ -134,6 +139,7 @@ Dev carve(void* workspace, const Layout& L) {
   d.part = (double*)(w + L.part);
   d.ebuf = (double*)(w + L.ebuf);
   d.nact_log = (int*)(w + L.nact_log);
+  d.xch = w + L.xch;
   return d;
 }
 
@@ -214,6 +220,7 @@ struct gd_ctx {
   long long n = 0;
   Consts c{};
   Dev d{};
+  Team team{};
   hipStream_t stream = nullptr;
   hipStream_t capture_stream = nullptr;
   // Two instances of the captured block steps, each ending with a copy of the
@@ -328,8 +335,12 @@ gd_status build_graph(gd_ctx* c, int ring) {
   GD_TRY(c->hip(hipStreamBeginCapture(c->capture_stream, hipStreamCaptureModeThreadLocal),
                 "begin capture"));
   gd_status st = GD_OK;
-  for (int k = 0; k < kGraphSteps && st == GD_OK; ++k)
-    st = enqueue_step(c, c->capture_stream, k & 1, nullptr, nullptr);
+  // With a team: the small steps that come next, then a step of any size.
+  const int rounds = c->team.wgs ? kTeamRounds : kGraphSteps;
+  for (int k = 0; k < rounds && st == GD_OK; ++k) {
+    if (c->team.wgs) st = c->hip(launch_team(c->d, c->c, c->team, k & 1, c->capture_stream), "team kernel");
+    if (st == GD_OK) st = enqueue_step(c, c->capture_stream, k & 1, nullptr, nullptr);
+  }
   if (st == GD_OK) {
     hipLaunchKernelGGL(k_status_out, dim3(1), dim3(64), 0, c->capture_stream,
                        (const unsigned long long*)c->d.sc, (unsigned long long*)c->h_ring[ring]);
@@ -413,6 +424,7 @@ gd_status gd_init(gd_ctx** out, const gd_params* p, int64_t n, const double* m, 
   c->p = *p;
   c->n = n;
   c->c = make_consts(p, n, kmax, false);
+  c->team = make_team((int)n, ipl_of(c->c), n1_of(c->c), false);
   c->stream = (hipStream_t)hip_stream;
   c->d = carve(workspace, L);
   Dev& d = c->d;
@@ -441,6 +453,8 @@ gd_status gd_init(gd_ctx** out, const gd_params* p, int64_t n, const double* m, 
   }
 
   c->d_eres = d.ebuf + 3 * (size_t)make_eplan((int)n).items;
+  if (c->team.wgs && (st = c->hip(launch_team_clear(d, c->team, c->stream), "team clear")) != GD_OK)
+    return cleanup_fail(st);
   if ((st = initialise(c, m, x, v)) != GD_OK) return cleanup_fail(st);
   *out = c;
   return GD_OK;
@@ -686,6 +700,9 @@ gd_status gd_step_to(gd_ctx* c, double t_end, gd_stats* st) {
   c->prog_t0 = c->prog_last = std::chrono::steady_clock::now();
   c->prog_target = t_end;
   GD_TRY(read_sched(c));
+  // (a team takes no step once its epochs are used up)
+  if (c->team.wgs && c->h_sc->team_epoch >= kTeamLastEpoch / 2)
+    GD_TRY(c->hip(launch_team_clear(c->d, c->team, c->stream), "team clear"));
   long long steps_before = c->h_sc->block_steps, pairs_before = c->h_sc->pairs;
   bool prepared = false;
   while (c->t_now < target) {

@@ -95,6 +95,10 @@ struct Sched {
   long long nact_hist[kNactBins];  // block steps by floor(log2 N_act)
   Plan plan;                 // force decomposition of the step in flight
   int hist[kMaxLevels + 1];  // particles per level
+  // Team kernel (k_team): workgroups that have started, and that have
+  // finished; launches to leave out.
+  int team_join, team_vote, team_skip;
+  unsigned team_epoch;  // steps published in the exchange lines since they were cleared
 };
 
 // The plan depends only on (n_act, n). The kernel that fixes n_act for a
@@ -183,6 +187,52 @@ __host__ __device__ inline EPlan make_eplan(int n) {
   return e;
 }
 
+// ---------------------------------------------------------------------------
+// Teams: small block steps in one resident kernel (k_team)
+// ---------------------------------------------------------------------------
+constexpr int kTeamBlock = 512;      // threads of a team's workgroup: one owned j each
+constexpr int kTeamWaves = kTeamBlock / 64;
+constexpr int kTeamMaxSlots = 64;    // j slices of the one-particle plan (one per lane of a wave)
+constexpr int kTeamMaxCap = 256;     // active particles of a step (LDS)
+constexpr int kTeamLine = 128;       // bytes of one exchange line (6 sums with their epochs)
+constexpr int kTeamPairs = 1 << 22;  // most pairs (n_act * n) of a team's step
+constexpr int kTeamSteps = 1024;     // most steps of one launch of a context's team
+constexpr unsigned kTeamLastEpoch = 0xFFFF0000u;
+
+// A team's workgroups share a cluster: workgroup w + wp * grp owns the j
+// slices w and (ks == 2) w + width, of the one-particle decomposition's s1
+// slices in slot order, and computes the active particles grp, grp + g, ...
+struct Team {
+  int wgs;    // workgroups (wp * g); 0: no team
+  int width;  // slots of the slice reduction per ks: correct_lanes(s1) / ks
+  int wp;     // owners of slices: min(width, s1)
+  int ks;     // slots per owner
+  int g;      // groups that share the active particles
+  int cap;    // most active particles of a step
+};
+
+// Exchange lines: two sets (the parity of the epoch) of rows lines per owner.
+__host__ __device__ inline int team_rows(const Team& t) { return t.cap > t.g ? t.cap : t.g; }
+__host__ __device__ inline size_t team_line_bytes(const Team& t) {
+  return (size_t)2 * team_rows(t) * t.wp * kTeamLine;
+}
+
+// LDS of a team's workgroup, laid out for the largest team (constant offsets:
+// with a layout per size the kernel ran out of scalar registers).
+struct TeamMem {
+  double tile[kTeamBlock / kTileJ][7][kTileJ];  // the owned j, predicted, and their masses
+  double own[12][kTeamBlock];                   // their state, and the times of their last corrections
+  long long tick[kTeamBlock];
+  int olev[kTeamBlock];                         // their levels
+  double st[12][kTeamMaxCap + 1];               // the set (last entry: the central particle)
+  double ftot[6][kTeamMaxCap];                  // summed forces, by place in the active list
+  double psum[kTeamMaxCap][2][6];               // sums over the owned slices
+  int idx[kTeamMaxCap], lev[kTeamMaxCap + 1];
+  int act[kTeamMaxCap];                         // entries of the active particles
+  int hist[64], wcnt[kTeamWaves];
+  int go, clamp, bad, stuck, bh;
+};
+
 // Device pointers of one context, carved from the caller's workspace.
 struct Dev {
   Sched* sc;
@@ -206,6 +256,7 @@ struct Dev {
   double* part;                            // [6][partial_rows(n)]: position * s + slot
   double* ebuf;                            // energy partials [items][3] + result [3]
   int* nact_log;                           // force-timing pass: N_act of each timed step
+  char* xch;                               // a team's exchange lines
 };
 
 struct Consts {
@@ -253,6 +304,34 @@ __host__ __device__ inline int correct_lanes(int s) {
   int l = 1;
   while (l < s && l < 64) l <<= 1;
   return l;
+}
+
+// The team of a cluster of n particles (wgs == 0: none). Steps run in a team
+// have the one-particle decomposition (at most n1 active), one slot per lane
+// of the slice reduction, and one owned j per thread.
+//   - ks: with slices of one tile and more than 32 of them, two per owner: an
+//     exchange among 64 owners took 2.3 us, among 32 2.0 us.
+//   - g: groups up to 128 workgroups in all share the pairs of a step: one
+//     largest step of N = 16384 took 60.6 ms with 32 workgroups (16 at
+//     N = 4096: 17.7 ms), 54.6 with 64, 52.3 with 128 (15.0 ms) and 52.3
+//     with 256.
+//   - cap: with 2^20 pairs as the most of a step instead of 2^22 N = 16384
+//     took 1.5 % more; the set's place in LDS ends it at 256 particles.
+inline Team make_team(int n, int ipl, int n1, bool pool) {
+  Team t{};
+  const Plan p1 = make_plan(1, n, ipl);
+  const int lanes = correct_lanes(p1.s);
+  if (p1.lj != 6 || ipl != kIPerLane || p1.s > kTeamMaxSlots || p1.len > kTeamBlock) return t;
+  t.ks = p1.len == kTileJ && lanes > (pool ? 1 : 32) ? 2 : 1;
+  t.width = lanes / t.ks;
+  t.wp = t.width < p1.s ? t.width : p1.s;
+  t.g = 1;
+  while (!pool && t.g < 8 && 2 * t.g * t.wp <= 128) t.g *= 2;
+  t.cap = kTeamPairs / n;
+  if (t.cap > kTeamMaxCap) t.cap = kTeamMaxCap;
+  if (t.cap > n1) t.cap = n1;
+  t.wgs = t.wp * t.g;
+  return t;
 }
 
 // Launch sizes for a context of n particles: enough workgroups for the
@@ -341,6 +420,11 @@ hipError_t launch_correct(const Dev& d, const Consts& c, hipStream_t s);
 hipError_t launch_step_force(const Dev& d, const Consts& c, int par, hipStream_t s,
                              hipEvent_t ev_start = nullptr, hipEvent_t ev_stop = nullptr);
 hipError_t launch_step_correct(const Dev& d, const Consts& c, int par, hipStream_t s);
+// The small block steps that come next, up to kTeamSteps, in one launch; ends
+// before a step of parity par, with its list prepared.
+hipError_t launch_team(const Dev& d, const Consts& c, const Team& t, int par, hipStream_t s);
+// Clears a team's exchange lines and its part of the schedule record.
+hipError_t launch_team_clear(const Dev& d, const Team& t, hipStream_t s);
 // Predicts every particle to the next block time and builds list 0 for it,
 // so that a step of parity 0 finds its list prepared.
 hipError_t launch_prepare(const Dev& d, const Consts& c, hipStream_t s);

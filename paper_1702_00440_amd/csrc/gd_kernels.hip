@@ -379,7 +379,7 @@ __device__ __forceinline__ int wg_append(bool take, int* counter) {
   return pos;
 }
 
-// k_step_correct's view of a context's arrays: the first array of each group
+// k_step_correct's (and k_team's) view of a context's arrays: the first array of each group
 // that the workspace layout places one stride apart (the state x .. jz, the j
 // stream px .. pvz, the list arrays ix .. ijz), with the two strides. Array k
 // of a group is addressed where it is used (st_arr, pj_arr, il_arr). Passing
@@ -393,8 +393,18 @@ struct DevC {
   unsigned char* lev;
   int *active, *ilev;
   long long* tag;
+  char* xch;
   long long sn, sl;  // strides in doubles: state and j stream; list arrays
 };
+
+__host__ __device__ inline DevC compact_view(const Dev& d) {
+  DevC e{};
+  e.sc = d.sc; e.m = d.m; e.jm = d.jm; e.st = d.x; e.pj = d.px; e.il = d.ix; e.part = d.part;
+  e.tick = d.tick; e.lev = d.lev; e.active = d.active; e.ilev = d.ilev; e.tag = d.tag; e.xch = d.xch;
+  e.sn = d.y - d.x;
+  e.sl = d.iy - d.ix;
+  return e;
+}
 
 // Array k of the state (x .. jz), j stream (px .. pvz) and list (ix .. ijz)
 // groups, for either view (k is a constant at every use; the j stream has the
@@ -522,7 +532,9 @@ struct ILane {
 // LJ lanes takes j = jsub, jsub + LJ, ...: a uniform trip count over whole
 // groups of LJ (scalar loop control, no per-lane exit masks), then at most
 // one partial group.
-template <bool kMaskSelf, bool kMixed, int kI>
+// kWhole: 64 lanes per i; a full tile's four j per lane are then unrolled, so
+// that their chains overlap where a wave has few i (k_team).
+template <bool kMaskSelf, bool kMixed, int kI, bool kWhole = false>
 __device__ __forceinline__ void tile_pairs(const double (*sj)[kTileJ], int cnt, int LJ, int jsub,
                                            int jt, double eps2, ILane<kI>& I) {
   const int full = cnt & ~(LJ - 1);
@@ -549,9 +561,14 @@ __device__ __forceinline__ void tile_pairs(const double (*sj)[kTileJ], int cnt, 
       }
     }
   };
+  if (kWhole && cnt == kTileJ) {
+#pragma unroll
+    for (int kk = 0; kk < kTileJ; kk += 64) pairs_with(kk + jsub);
+  } else {
 #pragma unroll 2
-  for (int kk = 0; kk < full; kk += LJ) pairs_with(kk + jsub);
-  if (full + jsub < cnt) pairs_with(full + jsub);
+    for (int kk = 0; kk < full; kk += LJ) pairs_with(kk + jsub);
+    if (full + jsub < cnt) pairs_with(full + jsub);
+  }
   if (kMixed) {
     // At most kTileJ / LJ acceleration terms per lane in FP32, then into FP64.
 #pragma unroll
@@ -752,6 +769,12 @@ __device__ __forceinline__ void force_body(const Dev& d, const Consts& c, int bl
     const long long prepared =
         (long long)(((unsigned long long)(unsigned)__builtin_amdgcn_readfirstlane((int)(word >> 32)) << 32) |
                     (unsigned)__builtin_amdgcn_readfirstlane((int)word));
+    if (blk == 0 && tid == 0) {
+      // (the team kernel before this one has ended)
+      sc->team_join = 0;
+      sc->team_vote = 0;
+      sc->team_skip = max(0, sc->team_skip - 1);
+    }
     if (nx.done) {
       if (blk == 0 && tid == 0) {
         sc->done = 1;
@@ -897,6 +920,47 @@ __device__ __forceinline__ bool finite6(const double f[6]) {
 #pragma unroll
   for (int q = 0; q < 6; ++q) ok = ok && isfinite(f[q]);
   return ok;
+}
+
+// The correction of one particle (level lv, a0 and j0 at the start of the
+// step, xp and vp predicted, f the new acceleration and jerk): xn, vn and the
+// new level nl. Returns whether the step was clamped at dt_min. Every kernel
+// that corrects uses this one sequence of operations.
+__device__ __forceinline__ bool correct_one(const Consts& c, long long t_next, int lv, const double (&a0)[3],
+                                            const double (&j0)[3], const double (&xp)[3], const double (&vp)[3],
+                                            const double (&f)[6], double (&xn)[3], double (&vn)[3], int& nl) {
+  // h and its powers are powers of two: dividing by h^2 and h^3 is the exact
+  // product with their reciprocals (from 1 / dt_min, scaled by 2^(lv - kmax)).
+  const double h = (double)(1LL << (c.kmax - lv)) * c.dt_min;
+  const double h2 = h * h, h3 = h2 * h;
+  const double ih = ldexp(c.inv_dt_min, lv - c.kmax);
+  const double ih2 = ih * ih, ih3 = ih2 * ih;
+  double a2[3], a3[3], a2e[3];
+#pragma unroll
+  for (int q = 0; q < 3; ++q) {
+    const double da = a0[q] - f[q];
+    a2[q] = (-6.0 * da - h * (4.0 * j0[q] + 2.0 * f[3 + q])) * ih2;
+    a3[q] = (12.0 * da + 6.0 * h * (j0[q] + f[3 + q])) * ih3;
+    xn[q] = xp[q] + a2[q] * (h2 * h2) / 24.0 + a3[q] * (h2 * h3) / 120.0;
+    vn[q] = vp[q] + a2[q] * h3 / 6.0 + a3[q] * (h2 * h2) / 24.0;
+    a2e[q] = a2[q] + h * a3[q];
+  }
+  const double na1 = norm3(f[0], f[1], f[2]);
+  const double nj1 = norm3(f[3], f[4], f[5]);
+  const double na2 = norm3(a2e[0], a2e[1], a2e[2]);
+  const double na3 = norm3(a3[0], a3[1], a3[2]);
+  const double dtstar = sqrt(c.eta * (na1 * na2 + nj1 * nj1) / (nj1 * na3 + na2 * na2));
+  const int kc = level_for(dtstar, c.dt_max, c.inv_dt_max, c.kmax);
+  if (kc >= lv) {
+    nl = kc;
+  } else if (lv >= 1 && (t_next & ((1LL << (c.kmax - lv + 1)) - 1)) == 0) {
+    nl = lv - 1;
+  } else {
+    nl = lv;
+  }
+  if (nl <= c.kmax) return false;
+  nl = c.kmax;
+  return true;
 }
 
 // ---------------------------------------------------------------------------
@@ -1049,39 +1113,8 @@ __device__ __forceinline__ void correct_body(const D& d, const Consts& c, int bl
     if (owner) {
       if (!finite6(f)) bk.bad = 1;
 
-      // h and its powers are powers of two: dividing by h^2 and h^3 is the exact
-      // product with their reciprocals (from 1 / dt_min, scaled by 2^(lv - kmax)).
-      const double h = (double)(1LL << (c.kmax - lv)) * c.dt_min;
-      const double h2 = h * h, h3 = h2 * h;
-      const double ih = ldexp(c.inv_dt_min, lv - c.kmax);
-      const double ih2 = ih * ih, ih3 = ih2 * ih;
-      double a2[3], a3[3], a2e[3], xn[3], vn[3];
-#pragma unroll
-      for (int q = 0; q < 3; ++q) {
-        const double da = a0[q] - f[q];
-        a2[q] = (-6.0 * da - h * (4.0 * j0[q] + 2.0 * f[3 + q])) * ih2;
-        a3[q] = (12.0 * da + 6.0 * h * (j0[q] + f[3 + q])) * ih3;
-        xn[q] = xp[q] + a2[q] * (h2 * h2) / 24.0 + a3[q] * (h2 * h3) / 120.0;
-        vn[q] = vp[q] + a2[q] * h3 / 6.0 + a3[q] * (h2 * h2) / 24.0;
-        a2e[q] = a2[q] + h * a3[q];
-      }
-      const double na1 = norm3(f[0], f[1], f[2]);
-      const double nj1 = norm3(f[3], f[4], f[5]);
-      const double na2 = norm3(a2e[0], a2e[1], a2e[2]);
-      const double na3 = norm3(a3[0], a3[1], a3[2]);
-      const double dtstar = sqrt(c.eta * (na1 * na2 + nj1 * nj1) / (nj1 * na3 + na2 * na2));
-      const int kc = level_for(dtstar, c.dt_max, c.inv_dt_max, c.kmax);
-      if (kc >= lv) {
-        nl = kc;
-      } else if (lv >= 1 && (t_next & ((1LL << (c.kmax - lv + 1)) - 1)) == 0) {
-        nl = lv - 1;
-      } else {
-        nl = lv;
-      }
-      if (nl > c.kmax) {
-        nl = c.kmax;
-        atomicAdd(&bk.clamp, 1);
-      }
+      double xn[3], vn[3];
+      if (correct_one(c, t_next, lv, a0, j0, xp, vp, f, xn, vn, nl)) atomicAdd(&bk.clamp, 1);
       st_arr(d, kX)[i] = xn[0]; st_arr(d, kY)[i] = xn[1]; st_arr(d, kZ)[i] = xn[2];
       st_arr(d, kVx)[i] = vn[0]; st_arr(d, kVy)[i] = vn[1]; st_arr(d, kVz)[i] = vn[2];
       st_arr(d, kAx)[i] = f[0]; st_arr(d, kAy)[i] = f[1]; st_arr(d, kAz)[i] = f[2];
@@ -1170,6 +1203,695 @@ __global__ __launch_bounds__(kBlock) void k_step_correct(DevC d, Consts c, int p
     predict_rest(d, c, blockIdx.x, nb, par);
   else
     correct_body<true>(d, c, blockIdx.x - nb, gridDim.x - nb, par);
+}
+
+// ---------------------------------------------------------------------------
+// Teams: the small block steps in one resident kernel
+// ---------------------------------------------------------------------------
+//
+// Three quarters of the steps have a few active particles. Two kernels per
+// step then take 8 us (N = 1024) to 12.5 us (N = 16384) for under 1 us of
+// pairs: launch boundaries, and a chain of dependent memory round trips in
+// each kernel. A team of up to 32 workgroups takes such steps one after the
+// other without a launch between them:
+//   - every workgroup keeps the schedule (clock, level histogram), the set of
+//     the finest particles (all those of a level of at least `floor`, at most
+//     cap of them) with their state in LDS, and the state of the j it owns in
+//     registers;
+//   - a step: the set's particles due at the next block time are active; each
+//     workgroup computes their sums over its own j slices and publishes them;
+//   - every workgroup reads all published sums and corrects all active
+//     particles, so that the set, the histogram and the clock stay alike
+//     everywhere and one exchange per step is enough.
+// The launch ends before a step that reaches below floor (it has other
+// particles), or has more than cap of them.
+// The sums are those of the one-particle decomposition in the same order, and
+// the correction has the same operations, so results are bitwise those of
+// k_step_force and k_step_correct.
+//
+// What bounds a step is latency: the exchange (1.2 us among 32 workgroups at
+// best: a store and a load that miss the L2s), then chains of dependent FP64
+// operations. So each wave finds the schedule by itself, a wave whose item has
+// one i predicts it in registers, eight lanes correct one particle, and
+// the workgroup synchronises three times a step.
+// Measured, one largest step (1/8 time unit) of a Plummer sphere, with the two
+// kernels alone -> with the team: N = 256 2.93 -> 1.63 ms, 1024 8.20 -> 5.26,
+// 4096 21.0 -> 14.5, 8192 31.2 -> 24.7, 16384 58.1 -> 52.6 ms. A step in a team
+// takes 6 to 7 us: the exchange 2, the sums 1.4, the correction 1.3, the
+// schedule and the prediction of the owned j 0.8.
+//
+// The exchange. A sum travels as 16 bytes {low word, epoch, high word, epoch}
+// in a line of its own per (active particle, owner), written and read with
+// device-scope accesses (sc1: coherent across the XCDs' L2s); a reader polls
+// the lines themselves until every epoch is the step's. A flag per workgroup
+// after the sums would be three trips one after the other (2.7 us), agent
+// fences write back and invalidate L2s (4.5 us and more). Two sets of lines
+// (epoch parity) are enough: a workgroup that publishes epoch k + 2 has read
+// every workgroup's lines of epoch k + 1, which each published after it had
+// read epoch k.
+//
+// All workgroups of a team must run at the same time, since they wait for one
+// another, and nothing promises that they do: others' kernels may hold the
+// compute units, and the driver may suspend and resume a queue. So every wait
+// is bounded and a launch can be called off, at two points:
+//   - joining (while the set is read): the team runs once all have started;
+//     a workgroup that has waited kJoinTicks calls the launch off, and the
+//     next kTeamSkip launches end at once (another stream holds the room);
+//   - the vote at the end: a launch writes nothing that a later kernel reads
+//     before all workgroups have finished its steps and said so. A workgroup
+//     whose wait in an exchange, or for the others' votes, has timed out calls
+//     it off.
+// Both go by one word that counts workgroups; calling off sets kTeamOff in it,
+// by an exchange that succeeds only while the count is short. So once a count
+// is full nobody calls off, and once somebody has, nobody sees it full. A
+// launch that was called off leaves its steps to the kernels that follow it.
+
+constexpr long long kJoinTicks = 3000;      // 30 us of the 100 MHz clock
+constexpr int kTeamSkip = 64;               // launches left out after one that did not find room
+constexpr long long kVoteTicks = 10000000;  // 100 ms
+constexpr int kStuckPolls = 1 << 16;    // of an exchange's lines: 10 ms and more
+constexpr int kTeamLevels = (kTeamMaxSlots * kTeamBlock + kTeamBlock * 16 - 1) / (kTeamBlock * 16);  // 16-byte loads of levels per thread
+
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+
+
+// Barrier of the workgroup for LDS alone: __syncthreads also waits for the
+// wave's global stores to complete (a published sum's takes 900 cycles).
+__device__ __forceinline__ void team_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// Waits until all wgs workgroups have added themselves to *word (thread 0 of
+// each, after it has added its own), at most ticks: whether they have.
+constexpr int kTeamOff = 1 << 30;
+__device__ __forceinline__ bool team_agreed(int* word, int wgs, long long ticks) {
+  const long long t0 = wall_clock64();
+  for (;;) {
+    int v = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (v == wgs) return true;
+    if (v & kTeamOff) return false;
+    if (wall_clock64() - t0 > ticks)
+      __hip_atomic_compare_exchange_strong(word, &v, v | kTeamOff, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                           __HIP_MEMORY_SCOPE_AGENT);
+  }
+}
+
+// What a workgroup of a team knows about its own j slices.
+struct TeamOwn {
+  int w, grp;     // owner index, group
+  int slices;     // owned slices (1 or 2)
+  int slice[2];   // their numbers
+  int tps, len;   // tiles (1 or 2) and j per slice
+  int lg_len;     // log2(len)
+  bool direct;    // one slice, in a team of several: its sums are published as they are
+};
+
+// Slice stored in slot q of s (the inverse of slice_slot).
+__device__ __forceinline__ int slot_slice(int q, int s) {
+  return (s & 7) ? q : (q % (s >> 3)) * 8 + q / (s >> 3);
+}
+
+// Time from entry e's last correction to t_next: a particle of level k was
+// last corrected at a multiple of its step.
+__device__ __forceinline__ double team_dt(const TeamMem& s, const Consts& c, int e, long long t_now,
+                                          long long t_next) {
+  const int sh = c.kmax - s.lev[e];
+  return (double)(t_next - ((t_now >> sh) << sh)) * c.dt_min;
+}
+
+// Entry e predicted to t_next.
+__device__ __forceinline__ void team_predict(const TeamMem& s, const Consts& c, int e, long long t_now,
+                                             long long t_next, double (&p)[6]) {
+  taylor6(team_dt(s, c, e, t_now, t_next), s.st[kX][e], s.st[kY][e], s.st[kZ][e], s.st[kVx][e], s.st[kVy][e],
+          s.st[kVz][e], s.st[kAx][e], s.st[kAy][e], s.st[kAz][e], s.st[kJx][e], s.st[kJy][e], s.st[kJz][e], p);
+}
+
+// Publishes sum comp of active particle u (see the exchange above).
+__device__ __forceinline__ void team_publish(const Team& t, const TeamOwn& o, __amdgpu_buffer_rsrc_t lines,
+                                             unsigned epoch, int u, int comp, double f) {
+  const unsigned long long b = (unsigned long long)__double_as_longlong(f);
+  const u32x4 v = {(unsigned)b, epoch, (unsigned)(b >> 32), epoch};
+  __builtin_amdgcn_raw_buffer_store_b128(
+      v, lines, (((epoch & 1) * team_rows(t) + u) * t.wp + o.w) * kTeamLine + comp * 16, 0, 16 /* sc1 */);
+}
+
+// Sums of kI active particles over one owned slice, by one wave (lanes split
+// the j as k_force's do with 64 lanes per i): published if the workgroup owns
+// one slice, else psum[unit][slice][6]. bh: the central particle's entry.
+template <bool kMaskSelf, bool kCentral, bool kMixed, int kI>
+__device__ __forceinline__ void team_item(const DevC& d, const Consts& c, const Team& t, const TeamOwn& o,
+                                          TeamMem& s, int unit, int units, int k, long long t_now,
+                                          long long t_next, int bh, __amdgpu_buffer_rsrc_t lines,
+                                          unsigned epoch) {
+  const int lane = threadIdx.x & 63;
+  ILane<kI> I;
+#pragma unroll
+  for (int q = 0; q < kI; ++q) {
+    const int e = s.act[o.grp + min(unit * kI + q, units - 1) * t.g];
+    double p[6];
+    team_predict(s, c, e, t_now, t_next, p);
+    I.g[q] = (kMaskSelf || kCentral) ? s.idx[e] : 0;
+    I.e2[q] = (kCentral && I.g[q] == c.bh) ? c.eps2_bh : c.eps2;
+    I.x[q] = p[0]; I.y[q] = p[1]; I.z[q] = p[2];
+    I.vx[q] = p[3]; I.vy[q] = p[4]; I.vz[q] = p[5];
+    I.A[q] = Acc6{0, 0, 0, 0, 0, 0};
+  }
+  const int j0 = o.slice[k] * o.len, j1 = min(c.n, j0 + o.len);
+  for (int tt = 0; tt < o.tps && j0 + tt * kTileJ < j1; ++tt) {
+    const int jt = j0 + tt * kTileJ;
+    tile_pairs<kMaskSelf, kMixed, kI, true>(s.tile[k + tt], min(kTileJ, j1 - jt), 64, lane, jt, c.eps2, I);
+  }
+  if (kCentral && o.slice[k] == 0 && lane == 0) {
+    double b[6];
+    team_predict(s, c, bh, t_now, t_next, b);
+    const double bm = d.m[c.bh];
+#pragma unroll
+    for (int q = 0; q < kI; ++q)
+      if (I.g[q] != c.bh)
+        pair_fp64(I.x[q], I.y[q], I.z[q], I.vx[q], I.vy[q], I.vz[q], b[0], b[1], b[2], b[3], b[4], b[5], bm,
+                  c.eps2_bh, I.A[q]);
+  }
+  double r[3];
+  if constexpr (kI == 2) {
+    double v[12];
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      v[6 * q + 0] = I.A[q].ax; v[6 * q + 1] = I.A[q].ay; v[6 * q + 2] = I.A[q].az;
+      v[6 * q + 3] = I.A[q].jx; v[6 * q + 4] = I.A[q].jy; v[6 * q + 5] = I.A[q].jz;
+    }
+    quarter_sums<64>(v, r);
+  } else {
+    // the same sums for one i: the acceleration in the lower half of the wave
+    double v[6] = {I.A[0].ax, I.A[0].ay, I.A[0].az, I.A[0].jx, I.A[0].jy, I.A[0].jz};
+#pragma unroll
+    for (int q = 0; q < 3; ++q) r[q] = split_add<32>(v[q], v[3 + q]);
+    xor_add<16>(r);
+    group_sum(r, 16);
+  }
+  // The first lane of each part of the wave that holds a 3-vector: four
+  // parts (two i), or two halves (one i).
+  constexpr int kPart = kI == 2 ? 16 : 32;
+  if ((lane & (kPart - 1)) == 0) {
+    const int u = unit * kI + (kI == 2 ? lane >> 5 : 0), comp = (lane & kPart) ? 3 : 0;
+    if (u < units) {
+      if (o.direct) {
+#pragma unroll
+        for (int q = 0; q < 3; ++q) team_publish(t, o, lines, epoch, o.grp + u * t.g, comp + q, 0.0 + r[q]);
+      } else {
+        double* p = s.psum[u][k] + comp;
+        p[0] = r[0]; p[1] = r[1]; p[2] = r[2];
+      }
+    }
+  }
+}
+
+// Reads the published sums of the entries of this wave (e = wave, wave +
+// kTeamWaves, ...), polling each line until its epochs are the step's, and
+// adds the owners' sums in the tree of force_sums: owner p's slots are p and
+// p + width (added before they were published), so what is left are the
+// levels width / 2, ..., 1. Lane 8 p' + c of load q holds component c of owner
+// 8 q + p'; kNq loads cover the owners. Returns false if a wait timed out.
+template <int kNq>
+__device__ __forceinline__ bool team_collect(const Team& t, __amdgpu_buffer_rsrc_t lines, unsigned epoch, int n_act,
+                                             TeamMem& s) {
+  constexpr int kBatch = 8 / kNq;  // entries whose loads are in flight together
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int comp = lane & 7;
+  const int rows = team_rows(t), ne = max(n_act, t.g);
+  const unsigned set = (epoch & 1) * (unsigned)rows;
+  bool fine = true;
+  for (int e0 = wave; e0 < ne; e0 += kTeamWaves * kBatch) {
+    u32x4 v[8];
+#pragma unroll
+    for (int x = 0; x < 8; ++x) v[x] = u32x4{0, 0, 0, 0};
+    bool ok;
+    int polls = 0;
+    do {
+#pragma unroll
+      for (int x = 0; x < 8; ++x) {
+        const int e = e0 + (x / kNq) * kTeamWaves;
+        if (e < ne)
+          v[x] = __builtin_amdgcn_raw_buffer_load_b128(
+              lines, ((set + e) * t.wp + (x % kNq) * 8) * kTeamLine + lane * 16, 0, 16 /* sc1 */);
+      }
+      asm volatile("" ::: "memory");  // a poll reads again
+      ok = true;
+#pragma unroll
+      for (int x = 0; x < 8; ++x)
+        if (e0 + (x / kNq) * kTeamWaves < ne && comp < 6 && (x % kNq) * 8 + (lane >> 3) < t.wp)
+          ok = ok && v[x].y == epoch && v[x].w == epoch;
+      ok = __all(ok);
+    } while (!ok && ++polls < kStuckPolls);
+    fine = fine && ok;
+#pragma unroll
+    for (int b = 0; b < kBatch; ++b) {
+      double f[kNq];
+#pragma unroll
+      for (int q = 0; q < kNq; ++q) {
+        const u32x4 w = v[b * kNq + q];
+        const bool in = q * 8 + (lane >> 3) < t.wp;
+        f[q] = in ? __longlong_as_double((long long)(((unsigned long long)w.z << 32) | w.x)) : 0.0;
+      }
+#pragma unroll
+      for (int h = kNq / 2; h > 0; h /= 2)
+#pragma unroll
+        for (int q = 0; q < h; ++q) f[q] += f[q + h];
+      if (t.width > 4) f[0] += xor_partner_d<32>(f[0]);
+      if (t.width > 2) f[0] += xor_partner_d<16>(f[0]);
+      if (t.width > 1) f[0] += xor_partner_d<8>(f[0]);
+      const int e = e0 + b * kTeamWaves;
+      if (lane < 6 && e < n_act) s.ftot[lane][e] = f[0];
+    }
+  }
+  return fine;
+}
+
+// Value of lane kQ of each quad of lanes.
+template <int kQ>
+__device__ __forceinline__ double quad_lane_d(double v) {
+  constexpr int kCtrl = kQ * 0x55;  // quad_perm [kQ, kQ, kQ, kQ]
+  const unsigned long long b = (unsigned long long)__double_as_longlong(v);
+  const unsigned lo = (unsigned)__builtin_amdgcn_mov_dpp((int)(unsigned)b, kCtrl, 0xF, 0xF, false);
+  const unsigned hi = (unsigned)__builtin_amdgcn_mov_dpp((int)(unsigned)(b >> 32), kCtrl, 0xF, 0xF, false);
+  return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+
+// norm3 of the vector whose components the first three lanes of a quad hold.
+__device__ __forceinline__ double quad_norm3(double v) {
+  const double s = v * v;
+  return sqrt(quad_lane_d<0>(s) + quad_lane_d<1>(s) + quad_lane_d<2>(s));
+}
+
+// correct_one by 8 lanes: the first quad holds the components of the position
+// and acceleration (f: the new acceleration), the second those of the velocity
+// and jerk (f: the new jerk); fa and fj are the new acceleration and jerk of
+// the lane's component in both. The operations on a component, and on the norms,
+// are those of correct_one in the same order. Returns the corrected position
+// or velocity component.
+__device__ __forceinline__ double team_correct(const Consts& c, long long t_next, int lv, bool vel, double x0,
+                                               double v0, double a0, double j0, double fa, double fj, int& nl,
+                                               bool& clamped) {
+  const double h = (double)(1LL << (c.kmax - lv)) * c.dt_min;
+  // the prediction (taylor6)
+  const double t2 = 0.5 * h, t3 = h * (1.0 / 3.0);
+  const double xp = fma(h, fma(t2, fma(t3, j0, a0), v0), x0);
+  const double vp = fma(h, fma(t2, j0, a0), v0);
+  const double h2 = h * h, h3 = h2 * h;
+  const double ih = ldexp(c.inv_dt_min, lv - c.kmax);
+  const double ih2 = ih * ih, ih3 = ih2 * ih;
+  const double da = a0 - fa;
+  const double a2 = (-6.0 * da - h * (4.0 * j0 + 2.0 * fj)) * ih2;
+  const double a3 = (12.0 * da + 6.0 * h * (j0 + fj)) * ih3;
+  const double a2e = a2 + h * a3;
+  const double m2 = vel ? h3 : h2 * h2, d2 = vel ? 6.0 : 24.0;
+  const double m3 = vel ? h2 * h2 : h2 * h3, d3 = vel ? 24.0 : 120.0;
+  const double out = (vel ? vp : xp) + a2 * m2 / d2 + a3 * m3 / d3;
+  const double n1 = quad_norm3(vel ? fj : fa), n2 = quad_norm3(vel ? a3 : a2e);
+  const double o1 = xor_partner_d<4>(n1), o2 = xor_partner_d<4>(n2);
+  const double na1 = vel ? o1 : n1, nj1 = vel ? n1 : o1, na2 = vel ? o2 : n2, na3 = vel ? n2 : o2;
+  const double dtstar = sqrt(c.eta * (na1 * na2 + nj1 * nj1) / (nj1 * na3 + na2 * na2));
+  const int kc = level_for(dtstar, c.dt_max, c.inv_dt_max, c.kmax);
+  if (kc >= lv) {
+    nl = kc;
+  } else if (lv >= 1 && (t_next & ((1LL << (c.kmax - lv + 1)) - 1)) == 0) {
+    nl = lv - 1;
+  } else {
+    nl = lv;
+  }
+  clamped = nl > c.kmax;
+  if (clamped) nl = c.kmax;
+  return out;
+}
+
+// Small block steps of one cluster by workgroup me of its team. par >= 0: a
+// context's team, which leaves the list of parity par and the j stream
+// prepared for the next step; par < 0: a pool's, whose predictor does that.
+template <bool kMaskSelf, bool kCentral, bool kMixed>
+__device__ __forceinline__ void team_body(const DevC& d, const Consts& c, const Team& t, int me, int max_steps,
+                                          int par) {
+  extern __shared__ __align__(16) char smem[];
+  TeamMem& s = *(TeamMem*)smem;
+  Sched* __restrict__ sc = d.sc;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int n = c.n, kmax = c.kmax;
+
+  // Every workgroup decides alike: the record is not written before all of
+  // them have joined.
+  const long long t_end = sc->t_end;
+  const long long t_start = sc->t_now;
+  long long t_now = t_start;
+  const unsigned epoch0 = sc->team_epoch;
+  unsigned epoch = epoch0;
+  {
+    const NextStep nx = schedule_wave(sc, c);
+    if (nx.done || nx.n_act > t.cap || epoch >= kTeamLastEpoch || sc->nonfinite || sc->team_skip > 0) return;
+  }
+
+  if (tid == 0) (void)__hip_atomic_fetch_add(&sc->team_join, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+
+  TeamOwn o;
+  o.w = me % t.wp;
+  o.grp = me / t.wp;
+  o.tps = ((n + kTileJ - 1) / kTileJ + c.s1 - 1) / c.s1;
+  o.len = o.tps * kTileJ;
+  o.lg_len = o.tps == 2 ? 9 : 8;
+  o.direct = t.ks == 1 && t.wgs > 1;
+  o.slices = t.ks == 2 && o.w + t.width < c.s1 ? 2 : 1;
+  o.slice[0] = slot_slice(o.w, c.s1);
+  o.slice[1] = o.slices == 2 ? slot_slice(o.w + t.width, c.s1) : 0;
+  const long long sn = d.sn;
+
+  // The owned j of this thread: place tid % 256 of tile tid / 256 (of the slice,
+  // or of the second slice).
+  const int ot = tid / kTileJ, ok = tid % kTileJ;
+  int j = -1;
+  {
+    const int sl = t.ks == 2 ? ot : 0;
+    if (sl < o.slices && (t.ks == 2 || ot < o.tps)) {
+      const int j0 = o.slice[sl] * o.len;
+      const int jj = j0 + (t.ks == 2 ? 0 : ot * kTileJ) + ok;
+      if (jj < min(n, j0 + o.len)) j = jj;
+    }
+  }
+  {
+    const PState ps = load_pstate(d, max(j, 0));
+    const double st[12] = {ps.x, ps.y, ps.z, ps.vx, ps.vy, ps.vz, ps.ax, ps.ay, ps.az, ps.jx, ps.jy, ps.jz};
+#pragma unroll
+    for (int q = 0; q < 12; ++q) s.own[q][tid] = st[q];
+    s.tick[tid] = ps.tick;
+    s.olev[tid] = ps.lev;
+    s.tile[ot][6][ok] = (kCentral ? d.jm : d.m)[max(j, 0)];
+  }
+  if (tid < 64) s.hist[tid] = tid <= kmax ? sc->hist[tid] : 0;
+  if (tid == 0) {
+    s.clamp = 0;
+    s.bad = 0;
+    s.stuck = 0;
+    // the list that is prepared at the end is built anew
+    if (me == 0 && par >= 0) __hip_atomic_store(&sc->lcnt[par], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+
+  const __amdgpu_buffer_rsrc_t lines =
+      __builtin_amdgcn_make_buffer_rsrc(d.xch, 0, (int)team_line_bytes(t), 0x00027000);
+  team_sync();
+  // The set: the lowest level from which on at most cap particles lie, and those.
+  int floor_lev, n_ent;
+  {
+    int tail = s.hist[lane];
+#pragma unroll
+    for (int k = 1; k < 64; k *= 2) {
+      const int u = __shfl_down(tail, k, 64);
+      if (lane + k < 64) tail += u;
+    }
+    floor_lev = __ffsll((long long)__ballot(tail <= t.cap)) - 1;
+    n_ent = __builtin_amdgcn_readlane(tail, floor_lev);
+  }
+  {
+    // This thread's levels: 16 bytes kTeamLevels times (as many as the
+    // particles need), and the bytes of at least floor_lev among them: bit 7
+    // of level + 128 - floor_lev.
+    const unsigned add = 0x01010101u * (unsigned)(128 - floor_lev);
+    const int per = (n + kTeamBlock * 16 - 1) / (kTeamBlock * 16);
+    const __amdgpu_buffer_rsrc_t levels =
+        __builtin_amdgcn_make_buffer_rsrc(d.lev, 0, (n + 15) & ~15, 0x00027000);
+    u32x4 v[kTeamLevels];
+#pragma unroll
+    for (int q = 0; q < kTeamLevels; ++q)
+      v[q] = __builtin_amdgcn_raw_buffer_load_b128(
+          levels, q < per ? (tid * per + q) * 16 : (n + 15) & ~15 /* nothing */, 0, 0);
+    unsigned m[4 * kTeamLevels];
+    int cnt = 0;
+#pragma unroll
+    for (int w = 0; w < 4 * kTeamLevels; ++w) {
+      const int left = n - ((tid * per + w / 4) * 16 + (w & 3) * 4);
+      m[w] = (v[w / 4][w & 3] + add) & 0x80808080u;
+      if (left < 4) m[w] &= left > 0 ? (1u << (8 * left)) - 1u : 0u;
+      if (w / 4 >= per) m[w] = 0;
+      cnt += __popc(m[w]);
+    }
+    int incl = cnt;
+#pragma unroll
+    for (int k = 1; k < 64; k *= 2) {
+      const int u = __shfl_up(incl, k, 64);
+      if (lane >= k) incl += u;
+    }
+    if (lane == 63) s.wcnt[wave] = incl;
+    if (tid == 0) {
+      s.bh = t.cap;
+      s.go = t.wgs == 1 || team_agreed(&sc->team_join, t.wgs, kJoinTicks);
+    }
+    team_sync();
+    if (!s.go) {
+      if (me == 0 && tid == 0) sc->team_skip = kTeamSkip;
+      return;
+    }
+    int at = incl - cnt;
+#pragma unroll
+    for (int w = 0; w < kTeamWaves; ++w) at += w < wave ? s.wcnt[w] : 0;
+    if (cnt > 0) {
+#pragma unroll
+      for (int w = 0; w < 4 * kTeamLevels; ++w)
+        for (unsigned b = m[w]; b; b &= b - 1) {
+          const int byte = (__ffs((int)b) - 1) / 8;
+          const int i = (tid * per + w / 4) * 16 + (w & 3) * 4 + byte;
+          if (at >= t.cap) break;  // (never: the histogram counts the same particles)
+          s.idx[at] = i;
+          s.lev[at] = (int)((v[w / 4][w & 3] >> (8 * byte)) & 255u);
+          if (kCentral && i == c.bh) s.bh = at;
+          ++at;
+        }
+    }
+    if (kCentral && tid == 0) s.lev[t.cap] = d.lev[c.bh];
+    team_sync();
+    const int q = tid & 15;
+    constexpr int kRows = kTeamBlock / 16;  // entries fetched together
+    for (int e0 = tid >> 4; e0 < n_ent + (kCentral ? 1 : 0); e0 += 4 * kRows) {
+      double x[4];
+      int to[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const int e = e0 + k * kRows;
+        to[k] = e < n_ent ? e : t.cap;  // (the central particle, if it is not in the set)
+        const int i = e < n_ent ? s.idx[e] : kCentral ? c.bh : 0;
+        x[k] = d.st[min(q, 11) * sn + i];
+      }
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+        if (q < 12) s.st[q][to[k]] = x[k];
+    }
+    team_sync();
+  }
+
+  long long psteps = 0, t_next = 0;
+  int steps = 0, kthr = 0;
+  int bin = 0;  // lane b: steps of 2^b <= n_act < 2^(b+1)
+  bool done = false;
+  for (;;) {
+    // The schedule (as next_step_wave), by every wave.
+    const int h = s.hist[lane], bad = s.bad | s.stuck;
+    int lv[kTeamMaxCap / 64];
+#pragma unroll
+    for (int b = 0; b < kTeamMaxCap / 64; ++b) lv[b] = s.lev[b * 64 + lane];
+    const unsigned long long occ = __ballot(h > 0);
+    const int fine_sh = kmax - (occ ? 63 - __clzll((long long)occ) : 0);
+    t_next = ((t_now >> fine_sh) + 1) << fine_sh;
+    kthr = max(0, kmax - (int)__builtin_ctzll((unsigned long long)t_next));
+    done = t_next > t_end;
+    if (done || steps >= max_steps || bad || kthr < floor_lev) break;
+    ++epoch;
+    // The active entries, counted by every wave.
+    int n_act = 0;
+#pragma unroll
+    for (int b = 0; b < kTeamMaxCap / 64; ++b) {
+      const bool in = b * 64 + lane < n_ent && lv[b] >= kthr;
+      const unsigned long long m = __ballot(in);
+      if (wave == 0 && in) s.act[n_act + __popcll(m & ((1ULL << lane) - 1ULL))] = b * 64 + lane;
+      n_act += __popcll(m);
+    }
+    // The owned j predicted to t_next.
+    {
+      double p[6];
+      taylor6((double)(t_next - s.tick[tid]) * c.dt_min, s.own[kX][tid], s.own[kY][tid], s.own[kZ][tid],
+              s.own[kVx][tid], s.own[kVy][tid], s.own[kVz][tid], s.own[kAx][tid], s.own[kAy][tid],
+              s.own[kAz][tid], s.own[kJx][tid], s.own[kJy][tid], s.own[kJz][tid], p);
+#pragma unroll
+      for (int q = 0; q < 6; ++q) s.tile[ot][q][ok] = p[q];
+    }
+    team_sync();
+    // Sums over the owned slices: one particle per wave and item while that
+    // keeps waves busy, else two.
+    const int units = n_act > o.grp ? (n_act - o.grp + t.g - 1) / t.g : 0;
+    const int bh = kCentral ? s.bh : 0;
+    if (units * o.slices <= kTeamWaves) {
+      if (wave < units * o.slices)
+        team_item<kMaskSelf, kCentral, kMixed, 1>(d, c, t, o, s, wave / o.slices, units, wave % o.slices, t_now,
+                                                  t_next, bh, lines, epoch);
+    } else {
+      for (int it = wave; it < (units + 1) / 2 * o.slices; it += kTeamWaves)
+        team_item<kMaskSelf, kCentral, kMixed, 2>(d, c, t, o, s, it / o.slices, units, it % o.slices, t_now,
+                                                  t_next, bh, lines, epoch);
+    }
+    // Sums of two slices, added first; and a group without a particle publishes
+    // an empty entry, so that every workgroup is waited for in every exchange.
+    team_sync();  // (no wave still reads the set when another corrects it)
+    if (!o.direct || units == 0)
+      for (int x = tid; x < max(units, 1) * 8; x += kTeamBlock) {
+        const int u = x >> 3, comp = x & 7, e = o.grp + u * t.g;
+        if (comp >= 6) continue;
+        double f = 0.0;
+        if (units) {
+          f = 0.0 + s.psum[u][0][comp];
+          if (o.slices == 2) f += 0.0 + s.psum[u][1][comp];
+        }
+        if (t.wgs > 1) team_publish(t, o, lines, epoch, e, comp, f);
+        else if (units) s.ftot[comp][e] = f;
+      }
+    if (t.wgs == 1) {
+      team_sync();
+    } else {
+      bool fine;
+      if (t.width > 32) fine = team_collect<8>(t, lines, epoch, n_act, s);
+      else if (t.width > 16) fine = team_collect<4>(t, lines, epoch, n_act, s);
+      else if (t.width > 8) fine = team_collect<2>(t, lines, epoch, n_act, s);
+      else fine = team_collect<1>(t, lines, epoch, n_act, s);
+      if (!fine) s.stuck = 1;
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup", "local");  // the wave's sums, read by its other lanes
+      __builtin_amdgcn_wave_barrier();
+    }
+    // Correction: 8 lanes per particle, of the wave that collected its sums.
+    for (int u0 = wave; u0 < n_act; u0 += 64) {
+      const int u = u0 + kTeamWaves * (lane >> 3);
+      const bool in = u < n_act;
+      const int uu = in ? u : u0, e = s.act[uu];
+      const int r = lane & 7, q = min(r & 3, 2);
+      const bool vel = r >= 4;
+      const int lv = s.lev[e];
+      const double fa = s.ftot[q][uu], fj = s.ftot[3 + q][uu];
+      int nl;
+      bool clamped;
+      const double out = team_correct(c, t_next, lv, vel, s.st[q][e], s.st[3 + q][e], s.st[6 + q][e], s.st[9 + q][e],
+                                      fa, fj, nl, clamped);
+      __builtin_amdgcn_wave_barrier();  // (every lane has read the entry)
+      if (!in || (r & 3) == 3) continue;
+      const double f = vel ? fj : fa;
+      s.st[(vel ? 3 : 0) + q][e] = out;
+      s.st[(vel ? 9 : 6) + q][e] = f;
+      if (!isfinite(f)) s.bad = 1;
+      const int i = s.idx[e];
+      const int slot = slice_slot((int)((unsigned)i >> o.lg_len), c.s1);
+      const bool mine = (slot & (t.width - 1)) == o.w;
+      const bool second = t.ks == 2 && slot >= t.width;
+      const int place = i - o.slice[second ? 1 : 0] * o.len + (second ? kTileJ : 0);
+      if (mine) {
+        s.own[(vel ? 3 : 0) + q][place] = out;
+        s.own[(vel ? 9 : 6) + q][place] = f;
+      }
+      if (r == 0) {
+        if (clamped) atomicAdd(&s.clamp, 1);
+        if (nl != lv) {
+          s.lev[e] = nl;
+          atomicAdd(&s.hist[lv], -1);
+          atomicAdd(&s.hist[nl], 1);
+        }
+        if (mine) {
+          s.tick[place] = t_next;
+          s.olev[place] = nl;
+        }
+      }
+    }
+    team_sync();
+    bin += lane == 31 - __clz(n_act);
+    psteps += n_act;
+    t_now = t_next;
+    ++steps;
+  }
+
+  // The vote.
+  if (tid == 0) {
+    if (t.wgs == 1) {
+      s.go = !s.stuck;
+    } else if (s.stuck) {
+      __hip_atomic_fetch_or(&sc->team_vote, kTeamOff, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      s.go = 0;
+    } else {
+      (void)__hip_atomic_fetch_add(&sc->team_vote, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      s.go = team_agreed(&sc->team_vote, t.wgs, kVoteTicks);
+    }
+  }
+  team_sync();
+  if (!s.go) {
+    // (no epoch that a workgroup may have published is used again)
+    if (me == 0 && tid == 0) sc->team_epoch = epoch0 + (unsigned)max_steps + 1u;
+    return;
+  }
+  // The corrected particles of the owned slices; the next step's list and j
+  // stream; the record.
+  if (o.grp == 0) {
+    PState ps{};
+    bool take = false;
+    double p[6];
+    if (j >= 0) {
+      ps.x = s.own[kX][tid]; ps.y = s.own[kY][tid]; ps.z = s.own[kZ][tid];
+      ps.vx = s.own[kVx][tid]; ps.vy = s.own[kVy][tid]; ps.vz = s.own[kVz][tid];
+      ps.ax = s.own[kAx][tid]; ps.ay = s.own[kAy][tid]; ps.az = s.own[kAz][tid];
+      ps.jx = s.own[kJx][tid]; ps.jy = s.own[kJy][tid]; ps.jz = s.own[kJz][tid];
+      ps.tick = s.tick[tid];
+      ps.lev = s.olev[tid];
+      if (ps.tick > t_start) {
+        st_arr(d, kX)[j] = ps.x; st_arr(d, kY)[j] = ps.y; st_arr(d, kZ)[j] = ps.z;
+        st_arr(d, kVx)[j] = ps.vx; st_arr(d, kVy)[j] = ps.vy; st_arr(d, kVz)[j] = ps.vz;
+        st_arr(d, kAx)[j] = ps.ax; st_arr(d, kAy)[j] = ps.ay; st_arr(d, kAz)[j] = ps.az;
+        st_arr(d, kJx)[j] = ps.jx; st_arr(d, kJy)[j] = ps.jy; st_arr(d, kJz)[j] = ps.jz;
+        d.tick[j] = ps.tick;
+        d.lev[j] = (unsigned char)ps.lev;
+      }
+    }
+    if (par >= 0 && !done && !s.bad) {
+      if (j >= 0) {
+        predict_store(d, j, (double)(t_next - ps.tick) * c.dt_min, ps, p);
+        take = ps.lev >= kthr;
+      }
+      const unsigned long long ball = __ballot(take);
+      int base = 0;
+      if (lane == 0 && ball) base = atomicAdd(&sc->lcnt[par], __popcll(ball));
+      base = __builtin_amdgcn_readfirstlane(base);
+      if (take)
+        list_store(d, n, par, base + __popcll(ball & ((1ULL << lane) - 1ULL)), j, p, ps.ax, ps.ay, ps.az, ps.jx,
+                   ps.jy, ps.jz, ps.lev, t_next);
+    }
+  }
+  if (me == 0) {
+    if (tid <= kmax) sc->hist[tid] = s.hist[tid];
+    if (tid < kNactBins) sc->nact_hist[tid] += bin;
+    if (tid == 0) {
+      sc->t_now = t_now;
+      sc->block_steps += steps;
+      sc->particle_steps += psteps;
+      sc->pairs += psteps * n;
+      sc->clamps += s.clamp;
+      if (s.bad) sc->nonfinite = 1;
+      sc->team_epoch = epoch;
+      if (par >= 0) sc->spec = done ? -2 : (t_next << 1) | par;
+    }
+  }
+}
+
+template <bool kMaskSelf, bool kCentral, bool kMixed>
+__global__ __launch_bounds__(kTeamBlock) void k_team(DevC d, Consts c, Team t, int par) {
+  team_body<kMaskSelf, kCentral, kMixed>(d, c, t, blockIdx.x, kTeamSteps, par);
+}
+
+__global__ void k_team_clear(Sched* __restrict__ sc, uint4* __restrict__ lines, int words) {
+  const int k = blockIdx.x * blockDim.x + threadIdx.x;
+  if (k < words) lines[k] = make_uint4(0, 0, 0, 0);
+  if (k == 0) {
+    sc->team_join = 0;
+    sc->team_vote = 0;
+    sc->team_skip = 0;
+    sc->team_epoch = 0;
+  }
 }
 
 // Prediction of every particle to the next block time into the j stream and
@@ -2235,11 +2957,7 @@ hipError_t launch_step_force(const Dev& d, const Consts& c, int par, hipStream_t
 }
 
 hipError_t launch_step_correct(const Dev& d, const Consts& c, int par, hipStream_t s) {
-  DevC e{};
-  e.sc = d.sc; e.m = d.m; e.jm = d.jm; e.st = d.x; e.pj = d.px; e.il = d.ix; e.part = d.part;
-  e.tick = d.tick; e.lev = d.lev; e.active = d.active; e.ilev = d.ilev; e.tag = d.tag;
-  e.sn = d.y - d.x;
-  e.sl = d.iy - d.ix;
+  const DevC e = compact_view(d);
   // (make_layout places each group one stride apart; any other layout is refused)
   const double* st[12] = {d.x, d.y, d.z, d.vx, d.vy, d.vz, d.ax, d.ay, d.az, d.jx, d.jy, d.jz};
   const double* pj[6] = {d.px, d.py, d.pz, d.pvx, d.pvy, d.pvz};
@@ -2248,6 +2966,22 @@ hipError_t launch_step_correct(const Dev& d, const Consts& c, int par, hipStream
     if (st[k] != d.x + k * e.sn || il[k] != d.ix + k * e.sl || (k < 6 && pj[k] != d.px + k * e.sn))
       return hipErrorInvalidValue;
   hipLaunchKernelGGL(k_step_correct, dim3(c.correct_grid + grid_for(c.n)), dim3(kBlock), 0, s, e, c, par);
+  return hipGetLastError();
+}
+
+hipError_t launch_team(const Dev& d, const Consts& c, const Team& t, int par, hipStream_t s) {
+  auto kern = c.mixed ? (c.bh >= 0 ? k_team<false, true, true>
+                                   : (c.eps2 > 0.0 ? k_team<false, false, true> : k_team<true, false, true>))
+                      : (c.bh >= 0 ? k_team<false, true, false>
+                                   : (c.eps2 > 0.0 ? k_team<false, false, false> : k_team<true, false, false>));
+  hipLaunchKernelGGL(kern, dim3(t.wgs), dim3(kTeamBlock), sizeof(TeamMem), s, compact_view(d), c, t, par);
+  return hipGetLastError();
+}
+
+hipError_t launch_team_clear(const Dev& d, const Team& t, hipStream_t s) {
+  const size_t words = team_line_bytes(t) / 16;
+  hipLaunchKernelGGL(k_team_clear, dim3(grid_for((int)words) + 1), dim3(kBlock), 0, s, d.sc, (uint4*)d.xch,
+                     (int)words);
   return hipGetLastError();
 }
 
