@@ -1132,6 +1132,7 @@ struct PoolSlotHost {
   std::chrono::steady_clock::time_point t_admit, t_done;
   Dev d{};
   Consts c{};
+  Team team{};
 };
 
 }  // namespace
@@ -1142,7 +1143,9 @@ struct gd_pool {
   int max_clusters = 0;
   hipStream_t stream = nullptr;
   hipStream_t capture_stream = nullptr;
-  hipGraphExec_t graph = nullptr;
+  // The captured replays: without and with teams (kPoolRounds).
+  hipGraphExec_t graph[2] = {nullptr, nullptr};
+  bool teams = false;  // every resident cluster has a team, and they all fit
   char* arena = nullptr;
   size_t arena_bytes = 0, heap_off = 0;
   PoolSlot* d_slots = nullptr;
@@ -1195,16 +1198,23 @@ bool pool_place(gd_pool* P, size_t bytes, size_t* off) {
 gd_status pool_upload_table(gd_pool* P) {
   PoolTable& t = *P->h_tab;
   t.count = 0;
-  int acc = 0;
+  int acc = 0, wgs = 0;
+  P->teams = true;
   for (int sl = 0; sl < P->max_clusters; ++sl) {
     const PoolSlotHost& s = P->slots[sl];
     if (!s.resident) continue;
     t.order[t.count] = sl;
     t.pred_off[t.count] = acc;
+    t.team_off[t.count] = wgs;
     acc += (int)((s.n + kBlock - 1) / kBlock);
+    wgs += s.team.wgs;
+    // (a cluster without a team would take one step per round)
+    P->teams = P->teams && s.team.wgs > 0;
     ++t.count;
   }
   t.pred_off[t.count] = acc;
+  t.team_off[t.count] = wgs;
+  P->teams = P->teams && wgs <= kPoolTeamWgs;
   GD_TRY(P->hip(hipMemcpyAsync(P->d_tab, P->h_tab, sizeof(PoolTable), hipMemcpyHostToDevice, P->stream),
                 "upload pool table"));
   // The staging buffer is reused by the next call: wait for the copy.
@@ -1221,22 +1231,26 @@ gd_status pool_energy(gd_pool* P, PoolSlotHost& s, double* e) {
   return GD_OK;
 }
 
-gd_status pool_build_graph(gd_pool* P) {
-  if (P->graph) return GD_OK;
+gd_status pool_build_graph(gd_pool* P, int teams) {
+  if (P->graph[teams]) return GD_OK;
+  const bool mixed = (P->p.flags & GD_FLAG_MIXED) != 0;
+  static_assert(kPoolRounds * (kPoolTeamSteps + 1) <= kPoolSteps, "a replay takes at most kPoolSteps steps");
+  const int rounds = teams ? kPoolRounds : kPoolSteps;
   hipGraph_t g = nullptr;
   GD_TRY(P->hip(hipStreamBeginCapture(P->capture_stream, hipStreamCaptureModeThreadLocal),
                 "begin capture"));
   hipError_t e = hipSuccess;
-  for (int k = 0; k < kPoolSteps && e == hipSuccess; ++k)
-    e = launch_pool_step(P->d_slots, P->d_tab, P->d_work, (P->p.flags & GD_FLAG_MIXED) != 0,
-                         P->capture_stream);
+  for (int k = 0; k < rounds && e == hipSuccess; ++k) {
+    if (teams) e = launch_pool_team(P->d_slots, P->d_tab, mixed, P->capture_stream);
+    if (e == hipSuccess) e = launch_pool_step(P->d_slots, P->d_tab, P->d_work, mixed, P->capture_stream);
+  }
   if (e == hipSuccess) e = launch_pool_status(P->d_slots, P->d_tab, P->d_status, P->capture_stream);
   hipError_t e2 = hipStreamEndCapture(P->capture_stream, &g);
   if (e != hipSuccess || e2 != hipSuccess) {
     if (g) (void)hipGraphDestroy(g);
     return P->hip(e != hipSuccess ? e : e2, "capture pool graph");
   }
-  e = hipGraphInstantiate(&P->graph, g, nullptr, nullptr, 0);
+  e = hipGraphInstantiate(&P->graph[teams], g, nullptr, nullptr, 0);
   (void)hipGraphDestroy(g);
   return P->hip(e, "instantiate pool graph");
 }
@@ -1339,6 +1353,7 @@ gd_status gd_pool_admit(gd_pool* P, int64_t n, const double* m, const double* x,
   s.t_end = (long long)q * (1LL << kmax);
   s.d = carve(P->arena + off, L);
   s.c = make_consts(&P->p, n, kmax, true);
+  s.team = make_team((int)n, ipl_of(s.c), n1_of(s.c), true);
   // Initialisation of the cluster (Sec. 2.4 steps 2-3) on the pool stream.
   auto undo = [&](gd_status st) {
     s = PoolSlotHost();
@@ -1346,6 +1361,7 @@ gd_status gd_pool_admit(gd_pool* P, int64_t n, const double* m, const double* x,
   };
   gd_status st;
   if ((st = P->hip(launch_reset_sched(s.d, 0, P->stream), "reset")) != GD_OK) return undo(st);
+  if (s.team.wgs && (st = P->hip(launch_team_clear(s.d, s.team, P->stream), "team clear")) != GD_OK) return undo(st);
   if ((st = P->hip(launch_load(s.d, s.c, m, x, v, P->stream), "load kernel")) != GD_OK) return undo(st);
   if ((st = P->hip(launch_predict(s.d, s.c, kPredAll, 0.0, P->stream), "predict kernel")) != GD_OK)
     return undo(st);
@@ -1363,6 +1379,7 @@ gd_status gd_pool_admit(gd_pool* P, int64_t n, const double* m, const double* x,
   // Descriptor, then the table that makes the cluster resident.
   P->h_slot->d = s.d;
   P->h_slot->c = s.c;
+  P->h_slot->t = s.team;
   if ((st = P->hip(hipMemcpyAsync(&P->d_slots[sl], P->h_slot, sizeof(PoolSlot), hipMemcpyHostToDevice,
                                   P->stream),
                    "upload slot")) != GD_OK)
@@ -1379,8 +1396,8 @@ gd_status gd_pool_run(gd_pool* P, int32_t* finished, int32_t* n_finished) {
   int resident = 0;
   for (const auto& s : P->slots) resident += s.resident;
   if (resident == 0) return GD_OK;
-  GD_TRY(pool_build_graph(P));
-  GD_TRY(P->hip(hipGraphLaunch(P->graph, P->stream), "pool graph launch"));
+  GD_TRY(pool_build_graph(P, P->teams));
+  GD_TRY(P->hip(hipGraphLaunch(P->graph[P->teams], P->stream), "pool graph launch"));
   GD_TRY(P->hip(hipMemcpyAsync(P->h_status, P->d_status, sizeof(PoolStatus) * P->max_clusters,
                                hipMemcpyDeviceToHost, P->stream),
                 "read pool status"));
@@ -1450,7 +1467,8 @@ gd_status gd_pool_resident(gd_pool* P, int32_t* count) {
 
 void gd_pool_destroy(gd_pool* P) {
   if (!P) return;
-  if (P->graph) (void)hipGraphExecDestroy(P->graph);
+  for (hipGraphExec_t g : P->graph)
+    if (g) (void)hipGraphExecDestroy(g);
   if (P->capture_stream) (void)hipStreamDestroy(P->capture_stream);
   if (P->h_status) (void)hipHostFree(P->h_status);
   if (P->h_tab) (void)hipHostFree(P->h_tab);

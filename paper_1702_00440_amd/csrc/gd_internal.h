@@ -316,7 +316,9 @@ __host__ __device__ inline int correct_lanes(int s) {
 //     N = 4096: 17.7 ms), 54.6 with 64, 52.3 with 128 (15.0 ms) and 52.3
 //     with 256.
 //   - cap: with 2^20 pairs as the most of a step instead of 2^22 N = 16384
-//     took 1.5 % more; the set's place in LDS ends it at 256 particles.
+//     took 1.5 % more; the set's place in LDS ends it at 256 particles. In a
+//     pool, 2^14 pairs per workgroup (4.4 us): the others' teams wait for the
+//     slowest (2^15 of them: 81.4 instead of 79.6 ms, 48 clusters).
 inline Team make_team(int n, int ipl, int n1, bool pool) {
   Team t{};
   const Plan p1 = make_plan(1, n, ipl);
@@ -327,7 +329,7 @@ inline Team make_team(int n, int ipl, int n1, bool pool) {
   t.wp = t.width < p1.s ? t.width : p1.s;
   t.g = 1;
   while (!pool && t.g < 8 && 2 * t.g * t.wp <= 128) t.g *= 2;
-  t.cap = kTeamPairs / n;
+  t.cap = (pool ? t.wp << 14 : kTeamPairs) / n;
   if (t.cap > kTeamMaxCap) t.cap = kTeamMaxCap;
   if (t.cap > n1) t.cap = n1;
   t.wgs = t.wp * t.g;
@@ -365,12 +367,25 @@ constexpr int kMaxPool = 256;
 struct PoolSlot {
   Dev d;
   Consts c;
+  Team t;
 };
+
+// With teams, a replay of a pool takes kPoolRounds times up to kPoolTeamSteps
+// steps in the teams and one of every cluster's in the packed launches. All
+// teams have to fit the chip (one workgroup per compute unit, by their LDS).
+// 48 clusters of 256 to 8192 to t = 1/8 took 87.9 ms without teams, 79.6 with
+// 8 x (3 + 1) steps, 84.2 with 4 x (7 + 1) and 90.9 with 16 x (1 + 1); 5
+// clusters 39.5, 33.2, 36.4 and 41.4 ms. (Rounds of a power of two of steps:
+// the clusters' large blocks then fall into the packed launches together.)
+constexpr int kPoolRounds = 8;
+constexpr int kPoolTeamSteps = 3;
+constexpr int kPoolTeamWgs = 256;
 
 struct PoolTable {
   int count;                   // resident clusters
   int order[kMaxPool];         // slot index of each resident cluster
   int pred_off[kMaxPool + 1];  // prefix sum of the clusters' predictor blocks
+  int team_off[kMaxPool + 1];  // prefix sum of the teams' workgroups
 };
 
 // A cluster's block step as the pool predictor fixed it: block size, block
@@ -398,6 +413,9 @@ struct PoolStatus {
   int done, nonfinite;
 };
 
+// The small block steps that come next of every resident cluster, up to
+// kPoolTeamSteps, in their teams.
+hipError_t launch_pool_team(const PoolSlot* slots, const PoolTable* tab, bool mixed, hipStream_t s);
 hipError_t launch_pool_step(const PoolSlot* slots, const PoolTable* tab, PoolWork* work, bool mixed,
                             hipStream_t s);
 // Lagrange radii of the ascending fractions frac[0..n_frac) into out[0..n_frac),

