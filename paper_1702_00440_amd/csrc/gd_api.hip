@@ -88,9 +88,7 @@ Layout make_layout(long long n, int ipl) {
   L.ilev = take(2 * sizeof(int) * (size_t)n);
   L.tag = take(2 * sizeof(long long) * (size_t)n);
   L.part = take(sizeof(double) * 6 * (size_t)partial_rows(n, ipl));
-  // At least kEnergyGrid entries: the diagnostics reuse the buffer for their results.
-  const long long eitems = std::max<long long>(make_eplan((int)n).items, kEnergyGrid);
-  L.ebuf = take(sizeof(double) * 3 * (size_t)(eitems + 1));
+  L.ebuf = take(sizeof(double) * 3 * kEnergyGrid);
   L.nact_log = take(sizeof(int) * 72);
   // (contexts of a size that has teams hold kIPerLane i per lane; a pool's
   // team of the same cluster has fewer owners and groups)
@@ -239,7 +237,6 @@ struct gd_ctx {
   int* h_nact = nullptr;    // pinned host copy of the N_act log
   Sched* h_sc = nullptr;    // pinned host mirror of the device record
   double* h_e = nullptr;    // pinned host energy result (3 doubles)
-  double* d_eres = nullptr; // device energy result
   int phase = kIdle;
   bool synced = true;       // every particle at t_now
   long long t_now = 0;      // host copy, valid when synced
@@ -295,10 +292,7 @@ gd_status read_sched(gd_ctx* c) {
 }
 
 gd_status energy_now(gd_ctx* c, int unsoft, double out[3]) {
-  GD_TRY(c->hip(launch_energy(c->d, c->c, unsoft, c->stream), "energy kernel"));
-  GD_TRY(c->hip(hipMemcpyAsync(c->h_e, c->d_eres, 3 * sizeof(double), hipMemcpyDeviceToHost,
-                               c->stream),
-                "read energy"));
+  GD_TRY(c->hip(launch_energy(c->d, c->c, unsoft, c->h_e, c->stream), "energy kernel"));
   GD_TRY(c->hip(hipStreamSynchronize(c->stream), "synchronise"));
   for (int k = 0; k < 3; ++k) out[k] = c->h_e[k];
   return GD_OK;
@@ -452,7 +446,6 @@ gd_status gd_init(gd_ctx** out, const gd_params* p, int64_t n, const double* m, 
       return cleanup_fail(st);
   }
 
-  c->d_eres = d.ebuf + 3 * (size_t)make_eplan((int)n).items;
   if (c->team.wgs && (st = c->hip(launch_team_clear(d, c->team, c->stream), "team clear")) != GD_OK)
     return cleanup_fail(st);
   if ((st = initialise(c, m, x, v)) != GD_OK) return cleanup_fail(st);
@@ -1222,10 +1215,7 @@ gd_status pool_upload_table(gd_pool* P) {
 }
 
 gd_status pool_energy(gd_pool* P, PoolSlotHost& s, double* e) {
-  GD_TRY(P->hip(launch_energy(s.d, s.c, 0, P->stream), "energy kernel"));
-  const double* res = s.d.ebuf + 3 * (size_t)make_eplan(s.c.n).items;
-  GD_TRY(P->hip(hipMemcpyAsync(P->h_e, res, 3 * sizeof(double), hipMemcpyDeviceToHost, P->stream),
-                "read energy"));
+  GD_TRY(P->hip(launch_energy(s.d, s.c, 0, P->h_e, P->stream), "energy kernel"));
   GD_TRY(P->hip(hipStreamSynchronize(P->stream), "synchronise"));
   *e = P->h_e[0] + P->h_e[1];
   return GD_OK;

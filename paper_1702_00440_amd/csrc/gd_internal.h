@@ -38,12 +38,14 @@ constexpr int kMinSlice = kTileJ;
 // (kBlock >> kMinLj) * ipl = 32 (or 64) particles, which keeps the number of
 // j slices (and so the partial sums to reduce) small for large blocks.
 constexpr int kMinLj = 4;
-// Energy: i particles per lane from kEnergyLargeN particles on (one below,
-// where four would leave most lanes idle), and the nominal number of
-// workgroups a call is split into.
-constexpr int kEnergyIPerLane = 4;
-constexpr int kEnergyLargeN = 16384;
-constexpr int kEnergyGrid = 1024;
+// Energy: i particles per lane from these sizes on (four, two), workgroups of a
+// call, and the items it is cut into at least (where slices of kEnergyMinLen j
+// allow).
+constexpr int kEnergyN4 = 65536;
+constexpr int kEnergyN2 = 4096;
+constexpr int kEnergyGrid = 2048;
+constexpr int kEnergyItems = 8192;
+constexpr int kEnergyMinLen = 32;
 // Maximum block-step level (dt = dt_max / 2^level).
 constexpr int kMaxLevels = 41;
 
@@ -166,24 +168,30 @@ constexpr long long partial_rows(long long n, int ipl) {
   return rows > n + 16 ? rows : n + 16;
 }
 
-// Energy decomposition: items are (i tile of kBlock * ipl, j slice). Slices
-// are whole LDS tiles; about 8 items per workgroup of the nominal grid keep
-// the tail of the launch short.
+// Energy decomposition: an item is an i tile of kBlock * ipl particles and a
+// slice of len j at or right of it (a power-of-two part of the tile). Tile a
+// has the slices a * q .. s0 - 1 of the whole row of slices, q to a tile, so
+// only pairs that are wanted make items, all of the same size but for those
+// on the diagonal.
 struct EPlan {
-  int ipl, nit, s, len, items;
+  int ipl, nit, q, s0, len, grid;
+  long long items;
 };
+__host__ __device__ inline long long eplan_before(const EPlan& e, long long a) {  // items of tiles < a
+  return a * e.s0 - e.q * (a * (a - 1) / 2);
+}
 __host__ __device__ inline EPlan make_eplan(int n) {
   EPlan e;
-  e.ipl = n >= kEnergyLargeN ? kEnergyIPerLane : 1;
+  e.ipl = n >= kEnergyN4 ? 4 : n >= kEnergyN2 ? 2 : 1;
   const int tile = kBlock * e.ipl;
   e.nit = (n + tile - 1) / tile;
-  const int max_s = (n + kTileJ - 1) / kTileJ;
-  int s = (8 * kEnergyGrid + e.nit - 1) / e.nit;
-  if (s > max_s) s = max_s;
-  if (s < 1) s = 1;
-  e.s = s;
-  e.len = (((n + s - 1) / s + kTileJ - 1) / kTileJ) * kTileJ;
-  e.items = e.nit * s;
+  for (e.q = 1;; e.q *= 2) {
+    e.len = tile / e.q;
+    e.s0 = (n + e.len - 1) / e.len;
+    e.items = eplan_before(e, e.nit);
+    if (e.items >= kEnergyItems || e.len <= kEnergyMinLen) break;
+  }
+  e.grid = e.items < kEnergyGrid ? (int)e.items : kEnergyGrid;
   return e;
 }
 
@@ -254,7 +262,7 @@ struct Dev {
   // (-1: never since the state was loaded).
   long long* tag;
   double* part;                            // [6][partial_rows(n)]: position * s + slot
-  double* ebuf;                            // energy partials [items][3] + result [3]
+  double* ebuf;                            // energy partials [grid][3]; results of the diagnostics
   int* nact_log;                           // force-timing pass: N_act of each timed step
   char* xch;                               // a team's exchange lines
 };
@@ -451,7 +459,9 @@ hipError_t launch_prepare(const Dev& d, const Consts& c, hipStream_t s);
 hipError_t launch_log_nact(const Dev& d, int* out, hipStream_t s);
 hipError_t launch_init_dt(const Dev& d, const Consts& c, hipStream_t s);
 hipError_t launch_reduce_out(const Dev& d, const Consts& c, double* acc, double* jerk, hipStream_t s);
-hipError_t launch_energy(const Dev& d, const Consts& c, int unsoft, hipStream_t s);
+// out: 3 doubles (kinetic, potential, unsoftened potential), memory the GPU can
+// write (the pinned result of the caller).
+hipError_t launch_energy(const Dev& d, const Consts& c, int unsoft, double* out, hipStream_t s);
 hipError_t launch_set_tend(const Dev& d, long long t_end, hipStream_t s);
 hipError_t launch_reset_sched(const Dev& d, long long t_now, hipStream_t s);
 // forced_lj > 0: the decomposition plan_with(n_act, n, forced_lj, forced_s)

@@ -2075,14 +2075,22 @@ __global__ __launch_bounds__(kBlock) void k_predict(Dev d, Consts c, int mode, d
 // Energy (Eq. (2), softened and unsoftened potentials)
 // ---------------------------------------------------------------------------
 //
-// The potential sums each pair once: a lane holds kI i particles
-// (EPlan::ipl) and sums phi_i = sum_{j > i} m_j / sqrt(r_ij^2 + eps_ij^2)
-// over the j of its item (i tile, j slice); the workgroup then reduces
-// -m_i phi_i (and the kinetic term, on slice 0) in a fixed tree, and a second
-// kernel sums the item partials in a fixed order. Tiles wholly left of the i
-// tile are skipped and only those that overlap it test j > i. The central
-// particle's column enters the tile with mass 0 and is added once for each
-// i below it, with its own softening, by the slice that holds it.
+// The potential sums each pair once: a lane holds kI i particles (EPlan::ipl)
+// and sums phi_i = sum_{j > i} m_j / sqrt(r_ij^2 + eps_ij^2) over the j of its
+// item (i tile, j slice); a workgroup goes through its items, adds -m_i phi_i
+// (and the kinetic term, with a tile's first slice), and reduces them in a
+// fixed tree at the end; a second kernel sums the workgroups in a fixed order.
+// Only the slices that overlap the i tile test j > i. The central particle's
+// column enters the tile with mass 0 and is added once for each i below it,
+// with its own softening, by the slice that holds it.
+//
+// What bounds it: FP64 issue (16 slots a pair with the inverse square root).
+// Items of equal size, none of them empty, and at least 8192 where the slices
+// allow keep the chip evenly loaded: with one item per (tile of 1024, slice of
+// 256) of the whole square, half of them empty, N = 16384 took 140 us and
+// N = 1024 21.6 us; now 93 and 6.8 us. From N = 65536 four i per lane share an
+// LDS read; a call there took 1150 us before and takes 1072 now (4096 items:
+// 1106; 2048: 1188), N = 262144 16.5 and 15.5 ms.
 template <int kI, bool kMask, bool kUnsoft>
 __device__ __forceinline__ void energy_tile(const double (*sj)[4], int cnt, int jt,
                                             const int (&ii)[kI],
@@ -2135,12 +2143,18 @@ __global__ __launch_bounds__(kBlock) void k_energy(int n, double eps2, double ep
   __shared__ __align__(16) double sj[kTileJ][4];
   __shared__ double red[3][kBlock];
   const int tid = threadIdx.x;
-  for (int item = blockIdx.x; item < e.items; item += gridDim.x) {
-    // The slice is rotated by the i tile: consecutive workgroups go to
-    // different XCDs, and under j > i the slices hold unequal work.
-    const int itile = item / e.s, slice = (item - itile * e.s + itile) % e.s;
+  double kin = 0.0, pot = 0.0, potu = 0.0;
+  for (long long item = blockIdx.x; item < e.items; item += gridDim.x) {
+    // The tile: the root of eplan_before(a) = item, then exactly.
+    const double h = e.s0 + 0.5 * e.q;
+    long long a = (long long)((h - sqrt(fmax(0.0, h * h - 2.0 * e.q * (double)item))) / e.q);
+    a = max(0LL, min(a, (long long)e.nit - 1));
+    while (a > 0 && eplan_before(e, a) > item) --a;
+    while (a + 1 < e.nit && eplan_before(e, a + 1) <= item) ++a;
+    const int k = __builtin_amdgcn_readfirstlane((int)(item - eplan_before(e, a)));
+    const int itile = __builtin_amdgcn_readfirstlane((int)a);
     const int i0 = itile * kBlock * kI;
-    const int j0 = min(n, slice * e.len), j1 = min(n, j0 + e.len);
+    const int j0 = (itile * e.q + k) * e.len, j1 = min(n, j0 + e.len);
     int ii[kI];
     double xi[kI], yi[kI], zi[kI], e2[kI], phi[kI], phiu[kI];
 #pragma unroll
@@ -2150,8 +2164,7 @@ __global__ __launch_bounds__(kBlock) void k_energy(int n, double eps2, double ep
       e2[q] = ii[q] == bh ? eps2_bh : eps2;
       phi[q] = 0.0; phiu[q] = 0.0;
     }
-    // i0 and j0 are multiples of kTileJ, so max(j0, i0) starts a tile.
-    for (int jt = max(j0, i0); jt < j1; jt += kTileJ) {
+    for (int jt = j0; jt < j1; jt += kTileJ) {
       const int cnt = min(kTileJ, j1 - jt);
       __syncthreads();
       if (tid < cnt) {
@@ -2176,7 +2189,6 @@ __global__ __launch_bounds__(kBlock) void k_energy(int n, double eps2, double ep
         if constexpr (kUnsoft) phiu[q] = fma(mb, rsqrt_fp64(r2), phiu[q]);
       }
     }
-    double kin = 0.0, pot = 0.0, potu = 0.0;
 #pragma unroll
     for (int q = 0; q < kI; ++q) {
       const int i = i0 + q * kBlock + tid;
@@ -2184,36 +2196,35 @@ __global__ __launch_bounds__(kBlock) void k_energy(int n, double eps2, double ep
         const double mi = m[i];
         pot -= mi * phi[q];
         potu -= mi * phiu[q];
-        if (slice == 0) kin += 0.5 * mi * fma(vz[i], vz[i], fma(vy[i], vy[i], vx[i] * vx[i]));
+        if (k == 0) kin += 0.5 * mi * fma(vz[i], vz[i], fma(vy[i], vy[i], vx[i] * vx[i]));
       }
     }
-    red[0][tid] = kin;
-    red[1][tid] = pot;
-    red[2][tid] = potu;
+  }
+  red[0][tid] = kin;
+  red[1][tid] = pot;
+  red[2][tid] = potu;
+  __syncthreads();
+  for (int w = kBlock / 2; w > 0; w >>= 1) {
+    if (tid < w) {
+      red[0][tid] += red[0][tid + w];
+      red[1][tid] += red[1][tid + w];
+      red[2][tid] += red[2][tid + w];
+    }
     __syncthreads();
-    for (int w = kBlock / 2; w > 0; w >>= 1) {
-      if (tid < w) {
-        red[0][tid] += red[0][tid + w];
-        red[1][tid] += red[1][tid + w];
-        red[2][tid] += red[2][tid + w];
-      }
-      __syncthreads();
-    }
-    if (tid == 0) {
-      ebuf[3 * item + 0] = red[0][0];
-      ebuf[3 * item + 1] = red[1][0];
-      ebuf[3 * item + 2] = red[2][0];
-    }
+  }
+  if (tid == 0) {
+    ebuf[3 * blockIdx.x + 0] = red[0][0];
+    ebuf[3 * blockIdx.x + 1] = red[1][0];
+    ebuf[3 * blockIdx.x + 2] = red[2][0];
   }
 }
 
-__global__ __launch_bounds__(kBlock) void k_energy_final(int n, double* __restrict__ ebuf,
+__global__ __launch_bounds__(kBlock) void k_energy_final(int count, const double* __restrict__ ebuf,
                                                          double* __restrict__ out) {
-  const EPlan e = make_eplan(n);
   __shared__ double red[3][kBlock];
   const int tid = threadIdx.x;
   double s0 = 0, s1 = 0, s2 = 0;
-  for (int it = tid; it < e.items; it += kBlock) {
+  for (int it = tid; it < count; it += kBlock) {
     s0 += ebuf[3 * it + 0];
     s1 += ebuf[3 * it + 1];
     s2 += ebuf[3 * it + 2];
@@ -2234,6 +2245,7 @@ __global__ __launch_bounds__(kBlock) void k_energy_final(int n, double* __restri
     out[0] = red[0][0];
     out[1] = red[1][0];
     out[2] = red[2][0];
+    __threadfence_system();
   }
 }
 
@@ -3028,17 +3040,16 @@ hipError_t launch_reduce_out(const Dev& d, const Consts& c, double* acc, double*
   return hipGetLastError();
 }
 
-hipError_t launch_energy(const Dev& d, const Consts& c, int unsoft, hipStream_t s) {
+hipError_t launch_energy(const Dev& d, const Consts& c, int unsoft, double* out, hipStream_t s) {
   const EPlan ep = make_eplan(c.n);
-  auto kern = ep.ipl == kEnergyIPerLane ? (unsoft ? k_energy<kEnergyIPerLane, true>
-                                                  : k_energy<kEnergyIPerLane, false>)
-                                        : (unsoft ? k_energy<1, true> : k_energy<1, false>);
-  hipLaunchKernelGGL(kern, dim3(ep.items), dim3(kBlock), 0, s, c.n, c.eps2, c.eps2_bh, c.bh, d.x,
-                     d.y, d.z, d.vx, d.vy, d.vz, d.m, d.ebuf);
+  auto kern = ep.ipl == 4   ? (unsoft ? k_energy<4, true> : k_energy<4, false>)
+              : ep.ipl == 2 ? (unsoft ? k_energy<2, true> : k_energy<2, false>)
+                            : (unsoft ? k_energy<1, true> : k_energy<1, false>);
+  hipLaunchKernelGGL(kern, dim3(ep.grid), dim3(kBlock), 0, s, c.n, c.eps2, c.eps2_bh, c.bh, d.x, d.y, d.z, d.vx,
+                     d.vy, d.vz, d.m, d.ebuf);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_energy_final, dim3(1), dim3(kBlock), 0, s, c.n, d.ebuf,
-                     d.ebuf + 3 * (size_t)ep.items);
+  hipLaunchKernelGGL(k_energy_final, dim3(1), dim3(kBlock), 0, s, ep.grid, d.ebuf, out);
   return hipGetLastError();
 }
 
