@@ -396,11 +396,9 @@ const char* gd_last_error(const gd_ctx* c);
  * capture, tight serving loops, harnesses that forbid hipMalloc): the
  * acceleration and jerk that gd_force computes for an index list, from the
  * caller's arrays, with no context and no workspace. The call allocates
- * nothing. Its intermediate arrays (the j stream, the listed particles'
- * state, the slice partials and the schedule record) live in one scratch
- * array of the library per GPU, about 11.3 MiB, held from the library's
- * first use on that GPU until the process ends; the first call on a device
- * looks up that device's copy.
+ * nothing. The slice partials live in one scratch array of the library per GPU,
+ * about 6 MiB, held from the library's first use on that GPU until the process
+ * ends; the first call on a device looks up that device's copy.
  *   p          parameters, validated as in gd_init; eps, eps_bh, bh_index and
  *              GD_FLAG_MIXED select the pair arithmetic
  *   n          particles, 2 <= n <= GD_NOALLOC_MAX_N

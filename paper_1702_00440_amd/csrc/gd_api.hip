@@ -235,6 +235,7 @@ struct gd_ctx {
   double bucket_ms[GD_PROFILE_BUCKETS] = {};
   long long bucket_launches[GD_PROFILE_BUCKETS] = {}, bucket_pairs[GD_PROFILE_BUCKETS] = {};
   int* h_nact = nullptr;    // pinned host copy of the N_act log
+  int* h_bad = nullptr;     // pinned: an index of gd_force's list was out of range
   Sched* h_sc = nullptr;    // pinned host mirror of the device record
   double* h_e = nullptr;    // pinned host energy result (3 doubles)
   int phase = kIdle;
@@ -432,9 +433,11 @@ gd_status gd_init(gd_ctx** out, const gd_params* p, int64_t n, const double* m, 
   if ((st = c->hip(hipHostMalloc((void**)&c->h_sc, sizeof(Sched), hipHostMallocDefault),
                    "pinned status buffer")) != GD_OK)
     return cleanup_fail(st);
+  // (the energy result, and the flag of gd_force's indices)
   if ((st = c->hip(hipHostMalloc((void**)&c->h_e, 4 * sizeof(double), hipHostMallocDefault),
                    "pinned energy buffer")) != GD_OK)
     return cleanup_fail(st);
+  c->h_bad = (int*)(c->h_e + 3);
   if ((st = c->hip(hipStreamCreateWithFlags(&c->capture_stream, hipStreamNonBlocking),
                    "capture stream")) != GD_OK)
     return cleanup_fail(st);
@@ -535,6 +538,32 @@ gd_status gd_predict(gd_ctx* c, const double* t) {
 
 namespace {
 
+// Arguments of an index list's force. The kernel may write the outputs itself
+// if each particle has one slice, unless they overlap what other workgroups
+// still read (the reduction writes them after the force kernel).
+ListArgs list_args(const int32_t* idx, int n_act, int64_t n, const Plan& plan, double* acc, double* jerk,
+                   const double* m, const double* x, const double* v, int* bad) {
+  ListArgs a{};
+  a.idx = idx;
+  a.n_act = n_act;
+  a.plan = plan;
+  a.acc = acc;
+  a.jerk = jerk;
+  a.x = x;
+  a.v = v;
+  a.bad = bad;
+  auto apart = [&](const void* p, size_t bytes) {
+    auto clear = [&](const double* o) {
+      const uintptr_t o0 = (uintptr_t)o, o1 = o0 + 24 * (size_t)n_act, p0 = (uintptr_t)p, p1 = p0 + bytes;
+      return !o || !p || o1 <= p0 || p1 <= o0;
+    };
+    return clear(acc) && clear(jerk);
+  };
+  a.direct = plan.s == 1 && apart(idx, 4 * (size_t)n_act) && apart(m, 8 * (size_t)n) && apart(x, 24 * (size_t)n) &&
+             apart(v, 24 * (size_t)n);
+  return a;
+}
+
 // The force of the current active set (idx == NULL) or of an index list,
 // with make_plan's decomposition (forced_lj == 0) or a forced one.
 gd_status force_of(gd_ctx* c, const int32_t* idx, int64_t n_act, double* acc, double* jerk, int forced_lj,
@@ -550,37 +579,36 @@ gd_status force_of(gd_ctx* c, const int32_t* idx, int64_t n_act, double* acc, do
       c->phase = kForcedExplicit;
       return GD_OK;
     }
-    GD_TRY(c->hip(launch_set_active(c->d, c->c, idx, (int)n_act, c->stream, forced_lj, forced_s), "set active"));
     c->phase = kForcedExplicit;
   }
-  // With timing on, an explicit list's launch records its own start and end.
-  const bool timed = c->prof && idx != nullptr;
-  GD_TRY(c->hip(launch_force(c->d, c->c, c->stream, timed ? c->ev_s[kGraphSteps] : nullptr,
-                             timed ? c->ev_e[kGraphSteps] : nullptr),
-                "force kernel"));
-  if (acc || jerk) GD_TRY(c->hip(launch_reduce_out(c->d, c->c, acc, jerk, c->stream), "force output"));
-  if (idx != nullptr) {
-    GD_TRY(read_sched(c));
-    if (timed) {
-      float ms = 0.f;
-      GD_TRY(c->hip(hipEventElapsedTime(&ms, c->ev_s[kGraphSteps], c->ev_e[kGraphSteps]), "event time"));
-      c->prof_ms += ms;
-      c->prof_launches += 1;
-      c->prof_pairs += n_act * c->n;
-      const int b = prof_bucket(n_act);
-      c->bucket_ms[b] += ms;
-      c->bucket_launches[b] += 1;
-      c->bucket_pairs[b] += n_act * c->n;
-    }
-    if (c->h_sc->bad_input) {
-      c->h_sc->bad_input = 0;
-      GD_TRY(c->hip(hipMemcpyAsync(&c->d.sc->bad_input, &c->h_sc->bad_input, sizeof(int),
-                                   hipMemcpyHostToDevice, c->stream),
-                    "clear flag"));
-      GD_TRY(c->hip(hipStreamSynchronize(c->stream), "synchronise"));
-      return c->fail(GD_EINVAL, "index out of range in idx");
-    }
+  if (idx == nullptr) {
+    GD_TRY(c->hip(launch_force(c->d, c->c, c->stream), "force kernel"));
+    if (acc || jerk) GD_TRY(c->hip(launch_reduce_out(c->d, c->c, acc, jerk, c->stream), "force output"));
+    return GD_OK;
   }
+  const int ipl = ipl_of(c->c);
+  *c->h_bad = 0;
+  const ListArgs a = list_args(idx, (int)n_act, c->n,
+                               forced_lj > 0 ? plan_with((int)n_act, (int)c->n, forced_lj, forced_s, ipl)
+                                             : make_plan((int)n_act, (int)c->n, ipl),
+                               acc, jerk, nullptr, nullptr, nullptr, c->h_bad);
+  // With timing on, the launch records its own start and end.
+  GD_TRY(c->hip(launch_list_force(c->d, c->c, a, c->stream, c->prof ? c->ev_s[kGraphSteps] : nullptr,
+                                  c->prof ? c->ev_e[kGraphSteps] : nullptr),
+                "force kernel"));
+  GD_TRY(c->hip(hipStreamSynchronize(c->stream), "synchronise"));
+  if (c->prof) {
+    float ms = 0.f;
+    GD_TRY(c->hip(hipEventElapsedTime(&ms, c->ev_s[kGraphSteps], c->ev_e[kGraphSteps]), "event time"));
+    c->prof_ms += ms;
+    c->prof_launches += 1;
+    c->prof_pairs += n_act * c->n;
+    const int b = prof_bucket(n_act);
+    c->bucket_ms[b] += ms;
+    c->bucket_launches[b] += 1;
+    c->bucket_pairs[b] += n_act * c->n;
+  }
+  if (*c->h_bad) return c->fail(GD_EINVAL, "index out of range in idx");
   return GD_OK;
 }
 
@@ -903,57 +931,19 @@ const char* gd_last_error(const gd_ctx* c) {
 // Force evaluation without device allocation (gd_force_noalloc)
 // ===========================================================================
 //
-// The arrays a context keeps in its workspace for one force evaluation (the
-// schedule record, the j stream, the listed particles' state and the slice
-// partials) live here in one file-scope device array per GPU. Host code never
-// uses the array's name as an address: the first call on a device resolves
-// that device's copy with hipGetSymbolAddress and keeps the pointer.
+// The slice partials, which a context keeps in its workspace, live here in one
+// file-scope device array per GPU; the particles are read from the caller's
+// arrays. Host code never uses the array's name as an address: the first call
+// on a device resolves that device's copy with hipGetSymbolAddress and keeps
+// the pointer.
 
 namespace {
 
 constexpr long long kNoallocMaxN = GD_NOALLOC_MAX_N;
 
-constexpr size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
-
-// Byte offsets of the arrays of one call with n particles.
-struct NoallocLayout {
-  size_t sc, jm, p[3], pv[3], active, ip[3], ipv[3], part, total;
-};
-
-constexpr NoallocLayout noalloc_layout(long long n) {
-  NoallocLayout L{};
-  size_t off = 0;
-  const size_t nd = sizeof(double) * (size_t)n;
-  L.sc = off;
-  off = align256(off + sizeof(Sched));
-  L.jm = off;
-  off = align256(off + nd);
-  for (int d = 0; d < 3; ++d) {
-    L.p[d] = off;
-    off = align256(off + nd);
-  }
-  for (int d = 0; d < 3; ++d) {
-    L.pv[d] = off;
-    off = align256(off + nd);
-  }
-  L.active = off;
-  off = align256(off + sizeof(int) * (size_t)n);
-  for (int d = 0; d < 3; ++d) {
-    L.ip[d] = off;
-    off = align256(off + nd);
-  }
-  for (int d = 0; d < 3; ++d) {
-    L.ipv[d] = off;
-    off = align256(off + nd);
-  }
-  L.part = off;
-  off = align256(off + sizeof(double) * 6 * (size_t)partial_rows(n, kIPerLane));
-  L.total = off;
-  return L;
-}
-
-// Every size up to the maximum fits: each offset grows with n.
-constexpr size_t kNoallocScratchBytes = noalloc_layout(kNoallocMaxN).total;
+// The slice partials of one call with n particles: every size up to the
+// maximum fits (partial_rows grows with n).
+constexpr size_t kNoallocScratchBytes = sizeof(double) * 6 * (size_t)partial_rows(kNoallocMaxN, kIPerLane);
 static_assert(kNoallocMaxN < kLargeN, "calls of this size hold two i per lane, as contexts do");
 
 }  // namespace
@@ -994,43 +984,6 @@ gd_status noalloc_scratch(void** out) {
 
 }  // namespace
 
-// The inputs of one gd_force_noalloc call in the force kernel's layout: the
-// j stream (structure of arrays; masses with the central particle's zeroed),
-// the listed particles' state by list position, and the schedule record of a
-// step with those n_act particles. A listed index outside [0, n) gives its
-// position a NaN state (so NaN output rows) and the list entry -1.
-__global__ void k_noalloc_load(Dev d, int n, int bh, int ipl, const double* __restrict__ m,
-                               const double* __restrict__ x, const double* __restrict__ v,
-                               const int32_t* __restrict__ idx, int n_act) {
-  const int t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t == 0) {
-    Sched* sc = d.sc;
-    sc->n_act = n_act;
-    sc->done = 0;
-    sc->nonfinite = 0;
-    sc->bad_input = 0;
-    sc->plan = make_plan(n_act, n, ipl);
-  }
-  if (t < n) {
-    d.px[t] = x[3 * t]; d.py[t] = x[3 * t + 1]; d.pz[t] = x[3 * t + 2];
-    d.pvx[t] = v[3 * t]; d.pvy[t] = v[3 * t + 1]; d.pvz[t] = v[3 * t + 2];
-    if (bh >= 0) d.jm[t] = t == bh ? 0.0 : m[t];
-  }
-  if (t < n_act) {
-    const int i = idx[t];
-    const bool ok = i >= 0 && i < n;
-    const int k = ok ? i : 0;
-    const double nan = __builtin_nan("");
-    d.active[t] = ok ? i : -1;
-    d.ix[t] = ok ? x[3 * k] : nan;
-    d.iy[t] = ok ? x[3 * k + 1] : nan;
-    d.iz[t] = ok ? x[3 * k + 2] : nan;
-    d.ivx[t] = ok ? v[3 * k] : nan;
-    d.ivy[t] = ok ? v[3 * k + 1] : nan;
-    d.ivz[t] = ok ? v[3 * k + 2] : nan;
-  }
-}
-
 extern "C" {
 
 gd_status gd_force_noalloc(const gd_params* p, int64_t n, const double* m, const double* x,
@@ -1050,42 +1003,15 @@ gd_status gd_force_noalloc(const gd_params* p, int64_t n, const double* m, const
   void* base = nullptr;
   GD_TRY(noalloc_scratch(&base));
 
-  const NoallocLayout L = noalloc_layout(n);
-  char* w = (char*)base;
+  // The slice partials lie in the scratch array; everything else is read from
+  // the caller's arrays.
   Dev d{};
-  d.sc = (Sched*)(w + L.sc);
   d.m = const_cast<double*>(m);  // read only
-  d.jm = (double*)(w + L.jm);
-  d.px = (double*)(w + L.p[0]);
-  d.py = (double*)(w + L.p[1]);
-  d.pz = (double*)(w + L.p[2]);
-  d.pvx = (double*)(w + L.pv[0]);
-  d.pvy = (double*)(w + L.pv[1]);
-  d.pvz = (double*)(w + L.pv[2]);
-  d.active = (int*)(w + L.active);
-  d.ix = (double*)(w + L.ip[0]);
-  d.iy = (double*)(w + L.ip[1]);
-  d.iz = (double*)(w + L.ip[2]);
-  d.ivx = (double*)(w + L.ipv[0]);
-  d.ivy = (double*)(w + L.ipv[1]);
-  d.ivz = (double*)(w + L.ipv[2]);
-  d.part = (double*)(w + L.part);
-
-  // The constants of a context of this size; the grids follow this call's
-  // own decomposition (the kernels' results do not depend on the grid).
-  Consts c = consts_of(p, n, kmax, kIPerLane);
-  const Plan plan = make_plan((int)n_act, (int)n, kIPerLane);
-  c.force_grid = std::min(plan.items, kForceGrid);
-  const long long lanes = n_act * correct_lanes(plan.s);
-  c.correct_grid = (int)std::min<long long>((lanes + kBlock - 1) / kBlock, kCorrectGrid);
-
-  hipStream_t s = (hipStream_t)hip_stream;
-  const int grid = (int)((n + kBlock - 1) / kBlock);
-  hipLaunchKernelGGL(k_noalloc_load, dim3(grid), dim3(kBlock), 0, s, d, (int)n, c.bh, kIPerLane, m, x,
-                     v, idx, (int)n_act);
-  hipError_t e = hipGetLastError();
-  if (e == hipSuccess) e = launch_force(d, c, s);
-  if (e == hipSuccess) e = launch_reduce_out(d, c, acc, jerk, s);
+  d.part = (double*)base;
+  const Consts c = consts_of(p, n, kmax, kIPerLane);
+  const ListArgs a = list_args(idx, (int)n_act, n, make_plan((int)n_act, (int)n, kIPerLane), acc, jerk, m, x, v,
+                               nullptr);
+  const hipError_t e = launch_list_force(d, c, a, (hipStream_t)hip_stream);
   if (e != hipSuccess) {
     g_init_error = std::string("force launch: ") + hipGetErrorString(e);
     return GD_EHIP;

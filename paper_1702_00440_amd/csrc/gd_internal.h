@@ -267,6 +267,20 @@ struct Dev {
   char* xch;                               // a team's exchange lines
 };
 
+// One force evaluation of an index list (gd_force with indices,
+// gd_force_noalloc): the host knows the block size, so the decomposition
+// comes as an argument, and the force kernel reads the caller's list itself.
+struct ListArgs {
+  const int32_t* idx;
+  int n_act;
+  int direct;          // 1: one slice per particle, the kernel writes acc and jerk
+  Plan plan;
+  double *acc, *jerk;  // (n_act, 3) outputs, either may be null
+  // The caller's rows (gd_force_noalloc), else null: the j stream of d.
+  const double *x, *v;
+  int* bad;            // set when an index is out of range (null: its row is NaN)
+};
+
 struct Consts {
   int n;
   int kmax;          // log2(dt_max / dt_min)
@@ -459,15 +473,15 @@ hipError_t launch_prepare(const Dev& d, const Consts& c, hipStream_t s);
 hipError_t launch_log_nact(const Dev& d, int* out, hipStream_t s);
 hipError_t launch_init_dt(const Dev& d, const Consts& c, hipStream_t s);
 hipError_t launch_reduce_out(const Dev& d, const Consts& c, double* acc, double* jerk, hipStream_t s);
+// The force of an index list, and its outputs. d.sc null: no record of
+// non-finite results is kept.
+hipError_t launch_list_force(const Dev& d, const Consts& c, const ListArgs& a, hipStream_t s,
+                             hipEvent_t ev_start = nullptr, hipEvent_t ev_stop = nullptr);
 // out: 3 doubles (kinetic, potential, unsoftened potential), memory the GPU can
 // write (the pinned result of the caller).
 hipError_t launch_energy(const Dev& d, const Consts& c, int unsoft, double* out, hipStream_t s);
 hipError_t launch_set_tend(const Dev& d, long long t_end, hipStream_t s);
 hipError_t launch_reset_sched(const Dev& d, long long t_now, hipStream_t s);
-// forced_lj > 0: the decomposition plan_with(n_act, n, forced_lj, forced_s)
-// instead of make_plan's.
-hipError_t launch_set_active(const Dev& d, const Consts& c, const int32_t* idx, int n_act, hipStream_t s,
-                             int forced_lj = 0, int forced_s = 0);
 hipError_t launch_copy_active(const Dev& d, const Consts& c, int32_t* idx, hipStream_t s);
 hipError_t launch_get_state(const Dev& d, const Consts& c, double* x, double* v, double* a,
                             double* jerk, double* t_i, double* dt_i, hipStream_t s);

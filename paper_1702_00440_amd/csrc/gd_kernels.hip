@@ -580,6 +580,10 @@ __device__ __forceinline__ void tile_pairs(const double (*sj)[kTileJ], int cnt, 
   }
 }
 
+__device__ __forceinline__ bool fin3(double a, double b, double c) {
+  return isfinite(a) && isfinite(b) && isfinite(c);
+}
+
 // Storage slot of slice sl among the s slices of one particle. When s is a
 // multiple of 8, item and workgroup index agree mod 8, so slice sl runs on
 // XCD sl % 8; its slices are stored together, and each XCD's L2 writes back
@@ -628,11 +632,13 @@ __device__ __forceinline__ void eighth_sums(const double (&v)[24], double (&t)[3
 // that holds it (LJ / (2 kI) lanes). The central particle's pairs (softened
 // with eps_bh, once per i, on slice 0; bx.. its predicted state) are added to
 // the first lane's sums before the reduction.
+// An index list's force with one slice per particle (la, direct) is stored
+// in the caller's rows instead.
 template <bool kCentral, int kI>
 __device__ __forceinline__ void finish_item(const Dev& d, const Consts& c, int LJ, int jsub,
                                             int slice, int s, int n_act, ILane<kI>& I, double bx,
                                             double by, double bz, double bvx, double bvy,
-                                            double bvz) {
+                                            double bvz, const ListArgs* la = nullptr) {
   static_assert(kI == 2 || kI == 4, "the reduction splits the sums of two or four i");
   if (kCentral && slice == 0 && jsub == 0) {
     const int b = c.bh;
@@ -669,7 +675,15 @@ __device__ __forceinline__ void finish_item(const Dev& d, const Consts& c, int L
     int pos;
     if constexpr (kI == 2) pos = q ? I.pos[1] : I.pos[0];
     else pos = q == 0 ? I.pos[0] : q == 1 ? I.pos[1] : q == 2 ? I.pos[2] : I.pos[3];
-    if (pos < n_act) {
+    if (pos < n_act && la && la->direct) {
+      // (as the reduction of one slice: 0 + its sum)
+      double* const o = comp ? la->jerk : la->acc;
+      const double f0 = 0.0 + t[0], f1 = 0.0 + t[1], f2 = 0.0 + t[2];
+      if (o) {
+        o[3 * (size_t)pos] = f0; o[3 * (size_t)pos + 1] = f1; o[3 * (size_t)pos + 2] = f2;
+      }
+      if (d.sc && !fin3(f0, f1, f2)) atomicOr(&d.sc->nonfinite, 1);
+    } else if (pos < n_act) {
       // part[component][position][slot], components part_cs apart
       const size_t cs = (size_t)c.part_cs;
       double* o = d.part + (size_t)pos * s + slice_slot(slice, s) + comp * cs;
@@ -682,10 +696,11 @@ __device__ __forceinline__ void finish_item(const Dev& d, const Consts& c, int L
 
 // kStep: the force kernel of a graph-replayed block step (k_step_force), with
 // the active list of parity par; otherwise that of a step whose predictor ran
-// before (list 0).
-template <bool kMaskSelf, bool kCentral, bool kMixed, int kI, bool kStep = false>
+// before (list 0). kSrc: where the particles are read from (see ListArgs).
+enum : int { kSrcList = 0, kSrcIndex, kSrcRows };
+template <bool kMaskSelf, bool kCentral, bool kMixed, int kI, bool kStep = false, int kSrc = kSrcList>
 __device__ __forceinline__ void force_body(const Dev& d, const Consts& c, int blk, int nblk, int par = 0,
-                                           const PoolStep* step = nullptr) {
+                                           const PoolStep* step = nullptr, const ListArgs* la = nullptr) {
   Sched* __restrict__ sc = d.sc;
   const int n = c.n;
   const size_t lo = (size_t)par * n;  // list offset
@@ -711,6 +726,26 @@ __device__ __forceinline__ void force_body(const Dev& d, const Consts& c, int bl
 #pragma unroll
     for (int q = 0; q < kI; ++q) {
       I.pos[q] = itile * it + ilane + q * ilanes;
+      I.A[q] = Acc6{0, 0, 0, 0, 0, 0};
+      if constexpr (kSrc != kSrcList) {
+        const int g = la->idx[min(I.pos[q], kc)];
+        const bool ok = g >= 0 && g < n;
+        const int i = ok ? g : 0;
+        if (!ok && la->bad) *la->bad = 1;
+        I.g[q] = ok || kSrc == kSrcIndex ? i : -1;
+        I.e2[q] = (kCentral && I.g[q] == c.bh) ? c.eps2_bh : c.eps2;
+        if constexpr (kSrc == kSrcIndex) {
+          I.x[q] = px[i]; I.y[q] = py[i]; I.z[q] = pz[i];
+          I.vx[q] = pvx[i]; I.vy[q] = pvy[i]; I.vz[q] = pvz[i];
+        } else {
+          const double* const x = la->x + 3 * (size_t)i;
+          const double* const v = la->v + 3 * (size_t)i;
+          const double nan = __builtin_nan("");
+          I.x[q] = ok ? x[0] : nan; I.y[q] = ok ? x[1] : nan; I.z[q] = ok ? x[2] : nan;
+          I.vx[q] = ok ? v[0] : nan; I.vy[q] = ok ? v[1] : nan; I.vz[q] = ok ? v[2] : nan;
+        }
+        continue;
+      }
       const size_t k = lo + min(I.pos[q], kc);
       I.g[q] = (kMaskSelf || kCentral) ? d.active[k] : 0;
       // Softening enters only as the addend of r.r, so a per-i value costs
@@ -722,7 +757,6 @@ __device__ __forceinline__ void force_body(const Dev& d, const Consts& c, int bl
       I.vx[q] = d.ivx[k];
       I.vy[q] = d.ivy[k];
       I.vz[q] = d.ivz[k];
-      I.A[q] = Acc6{0, 0, 0, 0, 0, 0};
     }
   };
   // Tile loads and LDS stores are lane-uniform (indices clamped into the
@@ -733,6 +767,14 @@ __device__ __forceinline__ void force_body(const Dev& d, const Consts& c, int bl
   double rx = 0, ry = 0, rz = 0, rvx = 0, rvy = 0, rvz = 0, rm = 0;
   auto load_tile = [&](int base, int j1) {
     const int j = min(base + tid, j1 - 1);
+    if constexpr (kSrc == kSrcRows) {
+      const double* const x = la->x + 3 * (size_t)j;
+      const double* const v = la->v + 3 * (size_t)j;
+      rx = x[0]; ry = x[1]; rz = x[2];
+      rvx = v[0]; rvy = v[1]; rvz = v[2];
+      rm = kCentral && j == c.bh ? 0.0 : d.m[j];
+      return;
+    }
     rx = px[j]; ry = py[j]; rz = pz[j];
     rvx = pvx[j]; rvy = pvy[j]; rvz = pvz[j];
     rm = pm[j];
@@ -743,7 +785,7 @@ __device__ __forceinline__ void force_body(const Dev& d, const Consts& c, int bl
   // workgroups. Those request their item before the schedule record is
   // read, so that the two memory round trips overlap; a step with another
   // decomposition loads its items afresh.
-  const bool spec = blk < c.s1;
+  const bool spec = kSrc == kSrcList && blk < c.s1;
   if (spec) {
     // Slices are whole tiles: s1 slices of ceil(tiles / s1) tiles each (the
     // slice length of plan_with for that slice count).
@@ -757,7 +799,10 @@ __device__ __forceinline__ void force_body(const Dev& d, const Consts& c, int bl
 
   int n_act;
   Plan p;
-  if constexpr (kStep) {
+  if constexpr (kSrc != kSrcList) {
+    n_act = la->n_act;
+    p = la->plan;
+  } else if constexpr (kStep) {
     // The step from the level histogram, in every wave (each wave gets the
     // same result), then the check of the prepared list and j stream.
     const NextStep nx = schedule_wave(sc, c);
@@ -853,16 +898,34 @@ __device__ __forceinline__ void force_body(const Dev& d, const Consts& c, int bl
     double bx = 0, by = 0, bz = 0, bvx = 0, bvy = 0, bvz = 0;
     if (kCentral) {
       const int b = c.bh;
-      bx = px[b]; by = py[b]; bz = pz[b];
-      bvx = pvx[b]; bvy = pvy[b]; bvz = pvz[b];
+      if constexpr (kSrc == kSrcRows) {
+        bx = la->x[3 * (size_t)b]; by = la->x[3 * (size_t)b + 1]; bz = la->x[3 * (size_t)b + 2];
+        bvx = la->v[3 * (size_t)b]; bvy = la->v[3 * (size_t)b + 1]; bvz = la->v[3 * (size_t)b + 2];
+      } else {
+        bx = px[b]; by = py[b]; bz = pz[b];
+        bvx = pvx[b]; bvy = pvy[b]; bvz = pvz[b];
+      }
     }
-    finish_item<kCentral, kI>(d, c, LJ, jsub, slice, p.s, n_act, I, bx, by, bz, bvx, bvy, bvz);
+    finish_item<kCentral, kI>(d, c, LJ, jsub, slice, p.s, n_act, I, bx, by, bz, bvx, bvy, bvz,
+                              kSrc != kSrcList ? la : nullptr);
   }
 }
 
 template <bool kMaskSelf, bool kCentral, bool kMixed, int kI>
 __global__ __launch_bounds__(kBlock) void k_force(Dev d, Consts c) {
   force_body<kMaskSelf, kCentral, kMixed, kI>(d, c, blockIdx.x, gridDim.x);
+}
+
+// The force kernel of an index list. A context's call took a kernel that
+// copied the list and the listed particles' state, the force, the reduction
+// and a copy of the record for the check of the indices; gd_force_noalloc a
+// kernel that copied everything into structure-of-arrays form first. All of
+// that is latency: read here, the list costs one more dependent load. A call
+// of 16 of 16384 particles (with its gd_predict): 27.1 -> 22.5 us; of 256
+// without a context 15.9 -> 9.6 us.
+template <bool kMaskSelf, bool kCentral, bool kMixed, int kI, int kSrc>
+__global__ __launch_bounds__(kBlock) void k_list_force(Dev d, Consts c, ListArgs a) {
+  force_body<kMaskSelf, kCentral, kMixed, kI, false, kSrc>(d, c, blockIdx.x, gridDim.x, 0, nullptr, &a);
 }
 
 // The force kernel of a graph-replayed block step of parity par (see Sched).
@@ -1947,13 +2010,10 @@ __global__ __launch_bounds__(kBlock) void k_init_dt(Dev d, Consts c) {
   book_flush(bk, sc, c.kmax, tid);
 }
 
-// Summed forces of the current active list as (n_act, 3) row-major arrays
-// (gd_force outputs; either may be null).
-__global__ __launch_bounds__(kBlock) void k_reduce_out(Dev d, Consts c, double* __restrict__ acc,
-                                                       double* __restrict__ jerk) {
-  Sched* __restrict__ sc = d.sc;
-  const int n_act = sc->n_act;
-  const Plan p = sc->plan;
+// Summed forces of n_act listed particles (plan p) as (n_act, 3) row-major
+// arrays (gd_force outputs; either may be null).
+__device__ __forceinline__ void reduce_out(const Dev& d, const Consts& c, int n_act, const Plan& p,
+                                           double* __restrict__ acc, double* __restrict__ jerk) {
   const int L = correct_lanes(p.s);
   const int per_wg = kBlock / L;
   const int tid = threadIdx.x;
@@ -1973,7 +2033,18 @@ __global__ __launch_bounds__(kBlock) void k_reduce_out(Dev d, Consts c, double* 
       jerk[3 * k] = f[3]; jerk[3 * k + 1] = f[4]; jerk[3 * k + 2] = f[5];
     }
   }
-  if (bad) atomicOr(&sc->nonfinite, 1);
+  if (bad && d.sc) atomicOr(&d.sc->nonfinite, 1);
+}
+
+// Of the active list of the schedule record.
+__global__ __launch_bounds__(kBlock) void k_reduce_out(Dev d, Consts c, double* __restrict__ acc,
+                                                       double* __restrict__ jerk) {
+  reduce_out(d, c, d.sc->n_act, d.sc->plan, acc, jerk);
+}
+
+// Of an index list.
+__global__ __launch_bounds__(kBlock) void k_list_out(Dev d, Consts c, ListArgs a) {
+  reduce_out(d, c, a.n_act, a.plan, a.acc, a.jerk);
 }
 
 // ---------------------------------------------------------------------------
@@ -2253,10 +2324,6 @@ __global__ __launch_bounds__(kBlock) void k_energy_final(int count, const double
 // State movement and small bookkeeping kernels
 // ---------------------------------------------------------------------------
 
-__device__ __forceinline__ bool fin3(double a, double b, double c) {
-  return isfinite(a) && isfinite(b) && isfinite(c);
-}
-
 // Row-major (n, 3) inputs to SoA; masses copied; validation of the inputs.
 __global__ void k_load(Sched* __restrict__ sc, int n, int bh, const double* __restrict__ m_in,
                        const double* __restrict__ x_in, const double* __restrict__ v_in,
@@ -2325,32 +2392,6 @@ __global__ void k_set_tend(Sched* __restrict__ sc, long long t_end) {
     sc->lcnt[1] = 0;
     sc->done = 0;
   }
-}
-
-// Explicit active list for gd_force(idx, ...): range-checked copy.
-__global__ void k_set_active(Sched* __restrict__ sc, int n, int ipl, int forced_lj, int forced_s,
-                             const int32_t* __restrict__ idx, int n_act, int* __restrict__ active, const double* __restrict__ px,
-                             const double* __restrict__ py, const double* __restrict__ pz,
-                             const double* __restrict__ pvx, const double* __restrict__ pvy,
-                             const double* __restrict__ pvz, double* __restrict__ ix,
-                             double* __restrict__ iy, double* __restrict__ iz,
-                             double* __restrict__ ivx, double* __restrict__ ivy,
-                             double* __restrict__ ivz) {
-  const int k = blockIdx.x * blockDim.x + threadIdx.x;
-  if (k == 0) {
-    sc->n_act = n_act;
-    sc->done = 0;
-    sc->plan = forced_lj > 0 ? plan_with(n_act, n, forced_lj, forced_s, ipl) : make_plan(n_act, n, ipl);
-  }
-  if (k >= n_act) return;
-  int i = idx[k];
-  if (i < 0 || i >= n) {
-    atomicOr(&sc->bad_input, 1);
-    i = 0;
-  }
-  active[k] = i;
-  ix[k] = px[i]; iy[k] = py[i]; iz[k] = pz[i];
-  ivx[k] = pvx[i]; ivy[k] = pvy[i]; ivz[k] = pvz[i];
 }
 
 __global__ void k_copy_active(const Sched* __restrict__ sc, const int* __restrict__ active,
@@ -2969,6 +3010,39 @@ hipError_t launch_force(const Dev& d, const Consts& c, hipStream_t s, hipEvent_t
   return hipGetLastError();
 }
 
+template <int kSrc>
+static auto list_kernel(const Consts& c) {
+  if constexpr (kSrc == kSrcIndex)
+    if (ipl_of(c) == kIPerLaneLarge)
+      return c.mixed ? (c.bh >= 0 ? k_list_force<false, true, true, kIPerLaneLarge, kSrc>
+                                  : k_list_force<false, false, true, kIPerLaneLarge, kSrc>)
+                     : (c.bh >= 0 ? k_list_force<false, true, false, kIPerLaneLarge, kSrc>
+                                  : k_list_force<false, false, false, kIPerLaneLarge, kSrc>);
+  return c.mixed ? (c.bh >= 0 ? k_list_force<false, true, true, kIPerLane, kSrc>
+                              : (c.eps2 > 0.0 ? k_list_force<false, false, true, kIPerLane, kSrc>
+                                              : k_list_force<true, false, true, kIPerLane, kSrc>))
+                 : (c.bh >= 0 ? k_list_force<false, true, false, kIPerLane, kSrc>
+                              : (c.eps2 > 0.0 ? k_list_force<false, false, false, kIPerLane, kSrc>
+                                              : k_list_force<true, false, false, kIPerLane, kSrc>));
+}
+
+hipError_t launch_list_force(const Dev& d, const Consts& c, const ListArgs& a, hipStream_t s, hipEvent_t ev_start,
+                             hipEvent_t ev_stop) {
+  auto kern = a.x ? list_kernel<kSrcRows>(c) : list_kernel<kSrcIndex>(c);
+  const dim3 grid(a.plan.items < kForceGrid ? a.plan.items : kForceGrid);
+  if (ev_start)
+    hipExtLaunchKernelGGL(kern, grid, dim3(kBlock), 0, s, ev_start, ev_stop, 0, d, c, a);
+  else
+    hipLaunchKernelGGL(kern, grid, dim3(kBlock), 0, s, d, c, a);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess || a.direct || !(a.acc || a.jerk)) return e;
+  const long long lanes = (long long)a.n_act * correct_lanes(a.plan.s);
+  const long long wgs = (lanes + kBlock - 1) / kBlock;
+  hipLaunchKernelGGL(k_list_out, dim3((unsigned)(wgs < kCorrectGrid ? wgs : kCorrectGrid)), dim3(kBlock), 0, s, d, c,
+                     a);
+  return hipGetLastError();
+}
+
 hipError_t launch_step_force(const Dev& d, const Consts& c, int par, hipStream_t s, hipEvent_t ev_start,
                              hipEvent_t ev_stop) {
   auto kern = ipl_of(c) == kIPerLaneLarge
@@ -3065,14 +3139,6 @@ hipError_t launch_log_nact(const Dev& d, int* out, hipStream_t s) {
 
 hipError_t launch_reset_sched(const Dev& d, long long t_now, hipStream_t s) {
   hipLaunchKernelGGL(k_reset_sched, dim3(1), dim3(64), 0, s, d.sc, t_now);
-  return hipGetLastError();
-}
-
-hipError_t launch_set_active(const Dev& d, const Consts& c, const int32_t* idx, int n_act,
-                             hipStream_t s, int forced_lj, int forced_s) {
-  hipLaunchKernelGGL(k_set_active, dim3(grid_for(n_act > 0 ? n_act : 1)), dim3(kBlock), 0, s,
-                     d.sc, c.n, ipl_of(c), forced_lj, forced_s, idx, n_act, d.active, d.px, d.py, d.pz, d.pvx, d.pvy, d.pvz, d.ix,
-                     d.iy, d.iz, d.ivx, d.ivy, d.ivz);
   return hipGetLastError();
 }
 
