@@ -360,10 +360,14 @@ gd_status initialise(gd_ctx* c, const double* m, const double* x, const double* 
   GD_TRY(c->hip(launch_reset_sched(d, 0, c->stream), "reset"));
   GD_TRY(c->hip(launch_load(d, c->c, m, x, v, c->stream), "load kernel"));
   GD_TRY(c->hip(launch_predict(d, c->c, kPredAll, 0.0, c->stream), "predict kernel"));
-  GD_TRY(c->hip(launch_force(d, c->c, c->stream, c->prof ? c->ev_s[kGraphSteps] : nullptr,
-                             c->prof ? c->ev_e[kGraphSteps] : nullptr),
-                "force kernel"));
-  GD_TRY(c->hip(launch_init_dt(d, c->c, c->stream), "init dt kernel"));
+  const hipEvent_t ev_s = c->prof ? c->ev_s[kGraphSteps] : nullptr, ev_e = c->prof ? c->ev_e[kGraphSteps] : nullptr;
+  const bool sym = sym_init(c->c);
+  if (sym) {
+    GD_TRY(c->hip(launch_sym_init(d, c->c, make_sym_plan(c->c), c->h_e, c->stream, ev_s, ev_e), "initial force"));
+  } else {
+    GD_TRY(c->hip(launch_force(d, c->c, c->stream, ev_s, ev_e), "force kernel"));
+    GD_TRY(c->hip(launch_init_dt(d, c->c, c->stream), "init dt kernel"));
+  }
   GD_TRY(read_sched(c));
   if (c->h_sc->bad_input) return c->fail(GD_EINVAL, "non-finite or negative input (m, x or v)");
   if (c->h_sc->nonfinite) return c->fail(GD_ENONFINITE, "non-finite initial acceleration or jerk");
@@ -378,8 +382,8 @@ gd_status initialise(gd_ctx* c, const double* m, const double* x, const double* 
     c->bucket_launches[b] += 1;
     c->bucket_pairs[b] += c->n * c->n;
   }
-  double e[3];
-  GD_TRY(energy_now(c, 0, e));
+  double e[3] = {c->h_e[0], c->h_e[1], 0.0};
+  if (!sym) GD_TRY(energy_now(c, 0, e));
   c->e0 = c->e_last = e[0] + e[1];
   c->t_now = 0;
   c->wall_s = 0.0;
@@ -1281,8 +1285,14 @@ gd_status gd_pool_admit(gd_pool* P, int64_t n, const double* m, const double* x,
   if ((st = P->hip(launch_load(s.d, s.c, m, x, v, P->stream), "load kernel")) != GD_OK) return undo(st);
   if ((st = P->hip(launch_predict(s.d, s.c, kPredAll, 0.0, P->stream), "predict kernel")) != GD_OK)
     return undo(st);
-  if ((st = P->hip(launch_force(s.d, s.c, P->stream), "force kernel")) != GD_OK) return undo(st);
-  if ((st = P->hip(launch_init_dt(s.d, s.c, P->stream), "init dt kernel")) != GD_OK) return undo(st);
+  const bool sym = sym_init(s.c);
+  if (sym) {
+    if ((st = P->hip(launch_sym_init(s.d, s.c, make_sym_plan(s.c), P->h_e, P->stream), "initial force")) != GD_OK)
+      return undo(st);
+  } else {
+    if ((st = P->hip(launch_force(s.d, s.c, P->stream), "force kernel")) != GD_OK) return undo(st);
+    if ((st = P->hip(launch_init_dt(s.d, s.c, P->stream), "init dt kernel")) != GD_OK) return undo(st);
+  }
   if ((st = P->hip(launch_set_tend(s.d, s.t_end, P->stream), "prepare")) != GD_OK) return undo(st);
   Sched chk;
   if ((st = P->hip(hipMemcpyAsync(&chk, s.d.sc, sizeof(Sched), hipMemcpyDeviceToHost, P->stream),
@@ -1291,7 +1301,8 @@ gd_status gd_pool_admit(gd_pool* P, int64_t n, const double* m, const double* x,
   if ((st = P->hip(hipStreamSynchronize(P->stream), "synchronise")) != GD_OK) return undo(st);
   if (chk.bad_input) return undo(P->fail(GD_EINVAL, "non-finite or negative input (m, x or v)"));
   if (chk.nonfinite) return undo(P->fail(GD_ENONFINITE, "non-finite initial acceleration or jerk"));
-  if ((st = pool_energy(P, s, &s.e0)) != GD_OK) return undo(st);
+  if (sym) s.e0 = P->h_e[0] + P->h_e[1];
+  else if ((st = pool_energy(P, s, &s.e0)) != GD_OK) return undo(st);
   // Descriptor, then the table that makes the cluster resident.
   P->h_slot->d = s.d;
   P->h_slot->c = s.c;

@@ -5,6 +5,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
+
 namespace gd {
 
 // Launch geometry. Every kernel runs 256-lane workgroups (4 wave64s).
@@ -358,6 +360,59 @@ inline Team make_team(int n, int ipl, int n1, bool pool) {
   return t;
 }
 
+// ---------------------------------------------------------------------------
+// The force of all particles, each pair once (k_sym_force)
+// ---------------------------------------------------------------------------
+constexpr int kSymBlock = 512;  // threads of a workgroup
+constexpr int kSymI = 4;        // i particles per lane
+constexpr int kSymTile = 512;   // j of an LDS tile
+constexpr int kSymSpan = 3;     // most successive d of a launch
+
+struct SymPlan {
+  int wi;           // waves along i: blocks of 64 * kSymI * wi particles
+  int nb;           // blocks
+  int span;         // successive d of a launch
+  long long items;  // pairs of blocks (b, b + d): item d * nb + b
+};
+
+// Accumulator array k: six components of n sums. The lists' predicted state,
+// acceleration and jerk are 24 n doubles in a row; the rest is in the buffer
+// of slice partials.
+__host__ __device__ inline double* sym_sums(const Dev& d, int n, int k) {
+  return k < 4 ? d.ix + (size_t)k * 6 * n : d.part + (size_t)(k - 4) * 6 * n;
+}
+
+// Whether a cluster's initial force takes each pair once: FP64 (the mixed
+// arithmetic is that of one side, and its rounding is part of its results),
+// one softening, and enough pairs of blocks for the chip. gd_reinit with the
+// forces one-sided and with this: N = 24576 1.01 and 1.12 ms, 32768 1.72 and
+// 1.39, 65536 6.4 and 4.0.
+constexpr int kSymN = 32768;
+// Blocks of four waves from here, below of two: N = 131072 takes 14.9 ms with
+// four and 16.0 with two, N = 100003 10.5 and 9.5.
+constexpr int kSymN4 = 131072;
+inline bool sym_init(const Consts& c) { return c.n >= kSymN && !c.mixed && c.bh < 0; }
+
+inline SymPlan make_sym_plan(const Consts& c) {
+  SymPlan p;
+  p.wi = c.n >= kSymN4 ? 4 : 2;
+  const int rows = 64 * kSymI * p.wi;
+  p.nb = (c.n + rows - 1) / rows;
+  p.items = (long long)p.nb * ((p.nb + 1) / 2) + (p.nb % 2 == 0 ? p.nb / 2 : 0);
+  // Three d where two leave workgroups idle, if the arrays have room (N =
+  // 32768: 192 workgroups instead of 128, 1.39 instead of 2.06 ms).
+  const long long arrays = 4 + c.part_cs / c.n;
+  for (p.span = 2; p.span < kSymSpan && 2 * (p.span + 1) <= arrays && p.span * p.nb < 256;) ++p.span;
+  return p;
+}
+// Where the launch that begins with item f ends: as many whole turns of the
+// chip's workgroups as a d has, at most span d, at most one energy partial
+// per item.
+inline long long sym_launch_end(const SymPlan& p, long long f) {
+  const long long chunk = std::min(kEnergyGrid, 256 * std::max(1, p.nb / 256));
+  return std::min(std::min(f + chunk, (f / p.nb + p.span) * p.nb), p.items);
+}
+
 // Launch sizes for a context of n particles: enough workgroups for the
 // largest force decomposition and corrector layout over all block sizes
 // (sampled), capped; kernels loop over anything beyond the grid.
@@ -472,6 +527,11 @@ hipError_t launch_prepare(const Dev& d, const Consts& c, hipStream_t s);
 // list) to *out.
 hipError_t launch_log_nact(const Dev& d, int* out, hipStream_t s);
 hipError_t launch_init_dt(const Dev& d, const Consts& c, hipStream_t s);
+// The force of every particle at t_now, its initial block step, and the energy
+// (out as launch_energy's, the third 0): instead of launch_force,
+// launch_init_dt and launch_energy.
+hipError_t launch_sym_init(const Dev& d, const Consts& c, const SymPlan& p, double* out, hipStream_t s,
+                           hipEvent_t ev_start = nullptr, hipEvent_t ev_stop = nullptr);
 hipError_t launch_reduce_out(const Dev& d, const Consts& c, double* acc, double* jerk, hipStream_t s);
 // The force of an index list, and its outputs. d.sc null: no record of
 // non-finite results is kept.

@@ -130,6 +130,13 @@ __device__ __forceinline__ int xor_partner_i(int v) {
   }
 }
 
+// The value of lane l + 1 (of lane 0 in lane 63): the wave rotated by one lane.
+__device__ __forceinline__ double wave_from_next(double v) {
+  const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), 0x134, 0xf, 0xf, false);
+  const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), 0x134, 0xf, 0xf, false);
+  return __hiloint2double(hi, lo);
+}
+
 template <int kOff>
 __device__ __forceinline__ double xor_partner_d(double v) {
   const unsigned long long b = (unsigned long long)__double_as_longlong(v);
@@ -1970,6 +1977,23 @@ __global__ __launch_bounds__(kBlock) void k_prepare(Dev d, Consts c) {
   if (blockIdx.x == 0 && threadIdx.x == 0) sc->spec = nx.t_next << 1;
 }
 
+// One particle's initial block step from its force, stored with it.
+__device__ __forceinline__ void init_one(const Dev& d, const Consts& c, LocalBook& bk, int i, long long t_now,
+                                         const double (&f)[6]) {
+  if (!finite6(f)) bk.bad = 1;
+  const double dtstar = c.eta * norm3(f[0], f[1], f[2]) / norm3(f[3], f[4], f[5]);
+  int nl = level_for(dtstar, c.dt_max, c.inv_dt_max, c.kmax);
+  if (nl > c.kmax) {
+    nl = c.kmax;
+    atomicAdd(&bk.clamp, 1);
+  }
+  d.ax[i] = f[0]; d.ay[i] = f[1]; d.az[i] = f[2];
+  d.jx[i] = f[3]; d.jy[i] = f[4]; d.jz[i] = f[5];
+  d.tick[i] = t_now;
+  d.lev[i] = (unsigned char)nl;
+  atomicAdd(&bk.hist[nl], 1);
+}
+
 // Initial block steps (Sec. 2.4 step 3; Sec. 3.2: the same eta from the
 // initial calculation on): dt* = eta |a| / |jerk|, quantised to the largest
 // dt_max / 2^k <= dt*, clamped at dt_min. Stores a, jerk, t_i = t_now and the
@@ -1993,20 +2017,238 @@ __global__ __launch_bounds__(kBlock) void k_init_dt(Dev d, Consts c) {
     double f[6];
     reduce_slices(d.part, p.s, c.part_cs, k, L, r, valid, f);
     if (r != 0 || !valid) continue;
-    if (!finite6(f)) bk.bad = 1;
-    const double dtstar = c.eta * norm3(f[0], f[1], f[2]) / norm3(f[3], f[4], f[5]);
-    int nl = level_for(dtstar, c.dt_max, c.inv_dt_max, c.kmax);
-    if (nl > c.kmax) {
-      nl = c.kmax;
-      atomicAdd(&bk.clamp, 1);
-    }
-    d.ax[i] = f[0]; d.ay[i] = f[1]; d.az[i] = f[2];
-    d.jx[i] = f[3]; d.jy[i] = f[4]; d.jz[i] = f[5];
-    d.tick[i] = t_now;
-    d.lev[i] = (unsigned char)nl;
-    atomicAdd(&bk.hist[nl], 1);
+    init_one(d, c, bk, i, t_now, f);
   }
   __syncthreads();
+  book_flush(bk, sc, c.kmax, tid);
+}
+
+// ---------------------------------------------------------------------------
+// The force of all particles on each other, each pair once
+// ---------------------------------------------------------------------------
+//
+// The initial force of a large cluster, and its energy (sym_init). What bounds
+// it is FP64 issue, and a pair (i, j) shares all but the accumulation with (j,
+// i): 44 slots for both and for the pair's potential, instead of 70 for the
+// two forces and 16 for the potential. The sums of i stay in registers and
+// those of j travel: a wave holds 64 * kSymI particles i and takes 64 j at a
+// time; lane l starts with j = l and hands the sums of its j to lane l - 1
+// after every step, so that after 64 steps each is back, complete, without an
+// atomic. A workgroup's kWi waves along i and kSymBlock / 64 / kWi along j go
+// through tiles of kSymTile j in LDS, where the j sums stay between the waves'
+// turns. A pair's terms are those of pair_fp64, bit by bit.
+//
+// Order of the sums: an item is a pair of blocks of i and j, (b, b + d) modulo
+// the number of blocks, d up to half of it. A launch holds items of a few
+// successive d, and there is an accumulator array for each side of each: no
+// two items of a launch share one, launches follow each other in the stream,
+// and so every sum has a fixed order. (One partial sum for each item instead
+// would take 0.8 GB at N = 262144.) The arrays are the active lists and the
+// slice partials, which nothing else uses before the first block step.
+//
+// gd_reinit of N = 262144 took 90.3 ms (force 72.7, energy 16.5) and takes
+// 57.0, 1.2e12 ordered pairs/s: 440 us for each launch of 256 items of 1024 by
+// 1024, where the slots alone are 405 us at the clock that FP64 leaves.
+template <bool kMask>
+__device__ __forceinline__ void sym_turn(const double (*sj)[kSymTile], int sub, int lane,
+                                         int n, int i0, int j0, double eps2, const double (&xi)[kSymI][7],
+                                         Acc6 (&A)[kSymI], double& pot, double (&f)[6]) {
+  const double* const base = &sj[0][sub * 64];
+  double nx[7];
+#pragma unroll
+  for (int q = 0; q < 7; ++q) nx[q] = base[q * kSymTile + lane];
+#pragma unroll 2
+  for (int k = 0; k < 64; ++k) {
+    const double xj = nx[0], yj = nx[1], zj = nx[2], vxj = nx[3], vyj = nx[4], vzj = nx[5], mj = nx[6];
+    const int at = (lane + k + 1) & 63;
+#pragma unroll
+    for (int q = 0; q < 7; ++q) nx[q] = base[q * kSymTile + at];
+    const int j = j0 + ((lane + k) & 63);
+#pragma unroll
+    for (int q = 0; q < kSymI; ++q) {
+      const double dx = xj - xi[q][0], dy = yj - xi[q][1], dz = zj - xi[q][2];
+      const double dvx = vxj - xi[q][3], dvy = vyj - xi[q][4], dvz = vzj - xi[q][5];
+      double s = fma(dz, dz, fma(dy, dy, fma(dx, dx, eps2)));
+      const double rv = fma(dz, dvz, fma(dy, dvy, dx * dvx));
+      double mjp = mj, mip = xi[q][6];
+      if constexpr (kMask) {
+        // itself, and the places past the last particle
+        const int i = i0 + q * 64 + lane;
+        const bool skip = i == j || i >= n || j >= n;
+        s = skip ? 1.0 : s;
+        mjp = skip ? 0.0 : mjp;
+        mip = skip ? 0.0 : mip;
+      }
+      const double r = rsqrt_fp64(s);
+      const double r2 = r * r;
+      const double mjr = mjp * r, mir = mip * r;
+      pot = fma(mip, mjr, pot);
+      const double mj3 = mjr * r2, mi3 = mir * r2;
+      const double b3 = (rv * r2) * -3.0;
+      const double wx = fma(b3, dx, dvx), wy = fma(b3, dy, dvy), wz = fma(b3, dz, dvz);
+      A[q].ax = fma(mj3, dx, A[q].ax);
+      A[q].ay = fma(mj3, dy, A[q].ay);
+      A[q].az = fma(mj3, dz, A[q].az);
+      A[q].jx = fma(mj3, wx, A[q].jx);
+      A[q].jy = fma(mj3, wy, A[q].jy);
+      A[q].jz = fma(mj3, wz, A[q].jz);
+      f[0] = fma(-mi3, dx, f[0]);
+      f[1] = fma(-mi3, dy, f[1]);
+      f[2] = fma(-mi3, dz, f[2]);
+      f[3] = fma(-mi3, wx, f[3]);
+      f[4] = fma(-mi3, wy, f[4]);
+      f[5] = fma(-mi3, wz, f[5]);
+    }
+#pragma unroll
+    for (int q = 0; q < 6; ++q) f[q] = wave_from_next(f[q]);
+  }
+}
+
+template <int kWi>
+__global__ __launch_bounds__(kSymBlock) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_sym_force(
+    Dev d, int n, int nb, int span, double eps2, long long first) {
+  constexpr int kWj = kSymBlock / 64 / kWi;      // waves along j
+  constexpr int kRows = kWi * 64 * kSymI;        // particles of a block
+  static_assert(kSymTile == kSymBlock, "one j per thread and tile");
+  static_assert(kRows % kSymTile == 0, "whole tiles");
+  static_assert(kWi * kWj * 64 == kSymTile, "one part of a tile per wave");
+  // the j, then the sums of their forces (and at the end those of the i)
+  __shared__ double sj[13][kSymTile];
+  double(*const sa)[kSymTile] = sj + 7;
+  static_assert(kWi * kWj / 2 * kSymI * 6 * 64 <= 13 * kSymTile, "half of the waves' i sums");
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wi = w % kWi, wj = w / kWi;
+  const long long item = first + blockIdx.x;
+  const int off = (int)(item / nb), b = (int)(item - (long long)off * nb);
+  const int bj = b + off < nb ? b + off : b + off - nb;
+  const bool mask = off == 0 || (bj == nb - 1 || b == nb - 1);
+  double* const out_i = sym_sums(d, n, 2 * (off % span));
+  double* const out_j = sym_sums(d, n, 2 * (off % span) + 1);
+
+  const int i0 = b * kRows + wi * 64 * kSymI;  // the wave's
+  double xi[kSymI][7];
+  Acc6 A[kSymI];
+#pragma unroll
+  for (int q = 0; q < kSymI; ++q) {
+    const int i = min(i0 + q * 64 + lane, n - 1);
+    xi[q][0] = d.x[i]; xi[q][1] = d.y[i]; xi[q][2] = d.z[i];
+    xi[q][3] = d.vx[i]; xi[q][4] = d.vy[i]; xi[q][5] = d.vz[i];
+    xi[q][6] = d.m[i];
+    A[q] = Acc6{0, 0, 0, 0, 0, 0};
+  }
+  double pot = 0.0;
+  for (int t = 0; t < kRows; t += kSymTile) {
+    const int j0 = bj * kRows + t;
+    if (j0 >= n) break;
+    const int j = min(j0 + tid, n - 1);
+    const double r0 = d.x[j], r1 = d.y[j], r2 = d.z[j], r3 = d.vx[j], r4 = d.vy[j], r5 = d.vz[j], r6 = d.m[j];
+    __syncthreads();
+    sj[0][tid] = r0; sj[1][tid] = r1; sj[2][tid] = r2;
+    sj[3][tid] = r3; sj[4][tid] = r4; sj[5][tid] = r5;
+    sj[6][tid] = r6;
+#pragma unroll
+    for (int q = 0; q < 6; ++q) sa[q][tid] = 0.0;
+    __syncthreads();
+    // The waves of one wj take the same kWi parts of 64 j, in turn.
+#pragma unroll 1
+    for (int p = 0; p < kWi; ++p) {
+      const int sub = wj * kWi + (wi + p) % kWi;
+      double f[6];
+#pragma unroll
+      for (int q = 0; q < 6; ++q) f[q] = sa[q][sub * 64 + lane];
+      if (mask) sym_turn<true>(sj, sub, lane, n, i0, j0 + sub * 64, eps2, xi, A, pot, f);
+      else sym_turn<false>(sj, sub, lane, n, i0, j0 + sub * 64, eps2, xi, A, pot, f);
+#pragma unroll
+      for (int q = 0; q < 6; ++q) sa[q][sub * 64 + lane] = f[q];
+      __syncthreads();
+    }
+    // (a block with itself: every pair came up from both sides)
+    if (off != 0 && j0 + tid < n) {
+#pragma unroll
+      for (int q = 0; q < 6; ++q) out_j[(size_t)q * n + j0 + tid] += sa[q][tid];
+    }
+  }
+  // The i sums over the waves along j, the upper half to the lower.
+  double* const ex = &sj[0][0];
+#pragma unroll
+  for (int half = kWj / 2; half > 0; half /= 2) {
+    __syncthreads();
+    if (wj >= half && wj < 2 * half) {
+#pragma unroll
+      for (int q = 0; q < kSymI; ++q) {
+        double* const o = ex + ((size_t)((wj - half) * kWi + wi) * kSymI + q) * 6 * 64 + lane;
+        o[0] = A[q].ax; o[64] = A[q].ay; o[128] = A[q].az;
+        o[192] = A[q].jx; o[256] = A[q].jy; o[320] = A[q].jz;
+      }
+    }
+    __syncthreads();
+    if (wj < half) {
+#pragma unroll
+      for (int q = 0; q < kSymI; ++q) {
+        const double* const o = ex + ((size_t)(wj * kWi + wi) * kSymI + q) * 6 * 64 + lane;
+        A[q].ax += o[0]; A[q].ay += o[64]; A[q].az += o[128];
+        A[q].jx += o[192]; A[q].jy += o[256]; A[q].jz += o[320];
+      }
+    }
+  }
+  if (wj == 0) {
+#pragma unroll
+    for (int q = 0; q < kSymI; ++q) {
+      const int i = i0 + q * 64 + lane;
+      if (i >= n) continue;
+      double* const o = out_i + i;
+      o[0] += A[q].ax; o[(size_t)n] += A[q].ay; o[(size_t)2 * n] += A[q].az;
+      o[(size_t)3 * n] += A[q].jx; o[(size_t)4 * n] += A[q].jy; o[(size_t)5 * n] += A[q].jz;
+    }
+  }
+  __syncthreads();
+  ex[tid] = pot;
+  __syncthreads();
+  for (int k = kSymBlock / 2; k > 0; k >>= 1) {
+    if (tid < k) ex[tid] += ex[tid + k];
+    __syncthreads();
+  }
+  if (tid == 0) d.ebuf[3 * blockIdx.x + 1] -= (off == 0 ? 0.5 : 1.0) * ex[0];
+}
+
+// The accumulators of k_sym_force and the energy partials cleared.
+__global__ __launch_bounds__(kBlock) void k_sym_clear(Dev d, int n, int span) {
+  const size_t first = (size_t)blockIdx.x * kBlock + threadIdx.x, step = (size_t)gridDim.x * kBlock;
+  for (int a = 0; a < 2 * span; ++a) {
+    double* const sums = sym_sums(d, n, a);
+    for (size_t k = first; k < (size_t)6 * n; k += step) sums[k] = 0.0;
+  }
+  for (size_t k = first; k < 3 * kEnergyGrid; k += step) d.ebuf[k] = 0.0;
+}
+
+// k_init_dt after k_sym_force, and the kinetic energy.
+__global__ __launch_bounds__(kBlock) void k_sym_init_dt(Dev d, Consts c, int span) {
+  Sched* __restrict__ sc = d.sc;
+  const int n = c.n;
+  const int tid = threadIdx.x;
+  __shared__ LocalBook bk;
+  __shared__ double red[kBlock];
+  book_init(bk, tid);
+  __syncthreads();
+  double kin = 0.0;
+  for (int i = blockIdx.x * kBlock + tid; i < n; i += gridDim.x * kBlock) {
+    double f[6] = {0, 0, 0, 0, 0, 0};
+    for (int a = 0; a < 2 * span; ++a) {
+      const double* const o = sym_sums(d, n, a) + i;
+#pragma unroll
+      for (int q = 0; q < 6; ++q) f[q] += o[(size_t)q * n];
+    }
+    init_one(d, c, bk, i, sc->t_now, f);
+    kin += 0.5 * d.m[i] * fma(d.vz[i], d.vz[i], fma(d.vy[i], d.vy[i], d.vx[i] * d.vx[i]));
+  }
+  red[tid] = kin;
+  __syncthreads();
+  for (int k = kBlock / 2; k > 0; k >>= 1) {
+    if (tid < k) red[tid] += red[tid + k];
+    __syncthreads();
+  }
+  if (tid == 0) d.ebuf[3 * blockIdx.x] = red[0];
   book_flush(bk, sc, c.kmax, tid);
 }
 
@@ -3105,6 +3347,28 @@ hipError_t launch_correct(const Dev& d, const Consts& c, hipStream_t s) {
 
 hipError_t launch_init_dt(const Dev& d, const Consts& c, hipStream_t s) {
   hipLaunchKernelGGL(k_init_dt, dim3(c.correct_grid), dim3(kBlock), 0, s, d, c);
+  return hipGetLastError();
+}
+
+hipError_t launch_sym_init(const Dev& d, const Consts& c, const SymPlan& p, double* out, hipStream_t s,
+                           hipEvent_t ev_start, hipEvent_t ev_stop) {
+  hipLaunchKernelGGL(k_sym_clear, dim3(kEnergyGrid), dim3(kBlock), 0, s, d, c.n, p.span);
+  hipError_t e = hipGetLastError();
+  auto kern = p.wi == 4 ? k_sym_force<4> : k_sym_force<2>;
+  for (long long f = 0; f < p.items && e == hipSuccess;) {
+    const long long end = sym_launch_end(p, f);
+    hipEvent_t s0 = f == 0 ? ev_start : nullptr, s1 = end == p.items ? ev_stop : nullptr;
+    if (s0 || s1)
+      hipExtLaunchKernelGGL(kern, dim3((unsigned)(end - f)), dim3(kSymBlock), 0, s, s0, s1, 0, d, c.n, p.nb, p.span, c.eps2, f);
+    else
+      hipLaunchKernelGGL(kern, dim3((unsigned)(end - f)), dim3(kSymBlock), 0, s, d, c.n, p.nb, p.span, c.eps2, f);
+    e = hipGetLastError();
+    f = end;
+  }
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(k_sym_init_dt, dim3(std::min(grid_for(c.n), kEnergyGrid)), dim3(kBlock), 0, s, d, c, p.span);
+  if ((e = hipGetLastError()) != hipSuccess) return e;
+  hipLaunchKernelGGL(k_energy_final, dim3(1), dim3(kBlock), 0, s, kEnergyGrid, d.ebuf, out);
   return hipGetLastError();
 }
 
