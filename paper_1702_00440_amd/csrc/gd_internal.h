@@ -200,8 +200,13 @@ __host__ __device__ inline EPlan make_eplan(int n) {
 // ---------------------------------------------------------------------------
 // Teams: small block steps in one resident kernel (k_team)
 // ---------------------------------------------------------------------------
-constexpr int kTeamBlock = 512;      // threads of a team's workgroup: one owned j each
+constexpr int kTeamBlock = 512;      // threads of a team's workgroup
 constexpr int kTeamWaves = kTeamBlock / 64;
+constexpr int kTeamTiles = 4;        // most tiles of owned j
+// Most active particles that every owner of all j computes by itself: with 4 or
+// 6 the same, with 16 N = 1024 took 5.34 instead of 4.98 ms (two rounds of
+// pairs for each wave take what the exchange does).
+constexpr int kTeamSolo = 8;
 constexpr int kTeamMaxSlots = 64;    // j slices of the one-particle plan (one per lane of a wave)
 constexpr int kTeamMaxCap = 256;     // active particles of a step (LDS)
 constexpr int kTeamLine = 128;       // bytes of one exchange line (6 sums with their epochs)
@@ -210,7 +215,7 @@ constexpr int kTeamSteps = 1024;     // most steps of one launch of a context's 
 constexpr unsigned kTeamLastEpoch = 0xFFFF0000u;
 
 // A team's workgroups share a cluster: workgroup w + wp * grp owns the j
-// slices w and (ks == 2) w + width, of the one-particle decomposition's s1
+// slices w, w + width, ... (ks of them), of the one-particle decomposition's s1
 // slices in slot order, and computes the active particles grp, grp + g, ...
 struct Team {
   int wgs;    // workgroups (wp * g); 0: no team
@@ -230,17 +235,15 @@ __host__ __device__ inline size_t team_line_bytes(const Team& t) {
 // LDS of a team's workgroup, laid out for the largest team (constant offsets:
 // with a layout per size the kernel ran out of scalar registers).
 struct TeamMem {
-  double tile[kTeamBlock / kTileJ][7][kTileJ];  // the owned j, predicted, and their masses
-  double own[12][kTeamBlock];                   // their state, and the times of their last corrections
-  long long tick[kTeamBlock];
-  int olev[kTeamBlock];                         // their levels
+  double tile[kTeamTiles][7][kTileJ];           // the owned j, predicted, and their masses
   double st[12][kTeamMaxCap + 1];               // the set (last entry: the central particle)
   double ftot[6][kTeamMaxCap];                  // summed forces, by place in the active list
-  double psum[kTeamMaxCap][2][6];               // sums over the owned slices
+  double psum[2 * kTeamMaxCap][6];              // sums over the owned slices
   int idx[kTeamMaxCap], lev[kTeamMaxCap + 1];
   int act[kTeamMaxCap];                         // entries of the active particles
   int hist[64], wcnt[kTeamWaves];
   int go, clamp, bad, stuck, bh;
+  short mem[kTeamTiles * kTileJ];               // entries of the owned j (-1: not in the set)
 };
 
 // Device pointers of one context, carved from the caller's workspace.
@@ -332,9 +335,12 @@ __host__ __device__ inline int correct_lanes(int s) {
 
 // The team of a cluster of n particles (wgs == 0: none). Steps run in a team
 // have the one-particle decomposition (at most n1 active), one slot per lane
-// of the slice reduction, and one owned j per thread.
+// of the slice reduction, and one owned j per thread (two where every owner has
+// all slices).
 //   - ks: with slices of one tile and more than 32 of them, two per owner: an
 //     exchange among 64 owners took 2.3 us, among 32 2.0 us.
+//   - In a context of at most four tiles every owner has all slices. 32 groups
+//     share its larger steps (N = 1024: 4.98 ms; 16 groups 5.14, 8 5.57).
 //   - g: groups up to 128 workgroups in all share the pairs of a step: one
 //     largest step of N = 16384 took 60.6 ms with 32 workgroups (16 at
 //     N = 4096: 17.7 ms), 54.6 with 64, 52.3 with 128 (15.0 ms) and 52.3
@@ -349,10 +355,11 @@ inline Team make_team(int n, int ipl, int n1, bool pool) {
   const int lanes = correct_lanes(p1.s);
   if (p1.lj != 6 || ipl != kIPerLane || p1.s > kTeamMaxSlots || p1.len > kTeamBlock) return t;
   t.ks = p1.len == kTileJ && lanes > (pool ? 1 : 32) ? 2 : 1;
+  if (!pool && p1.s * p1.len <= kTeamTiles * kTileJ) t.ks = lanes;
   t.width = lanes / t.ks;
   t.wp = t.width < p1.s ? t.width : p1.s;
   t.g = 1;
-  while (!pool && t.g < 8 && 2 * t.g * t.wp <= 128) t.g *= 2;
+  while (!pool && t.g < (t.wp == 1 ? 32 : 8) && 2 * t.g * t.wp <= 128) t.g *= 2;
   t.cap = (pool ? t.wp << 14 : kTeamPairs) / n;
   if (t.cap > kTeamMaxCap) t.cap = kTeamMaxCap;
   if (t.cap > n1) t.cap = n1;

@@ -15,6 +15,8 @@
 
 #include <hip/hip_ext.h>
 
+#include <type_traits>
+
 #include "gd_internal.h"
 
 namespace gd {
@@ -1286,13 +1288,15 @@ __global__ __launch_bounds__(kBlock) void k_step_correct(DevC d, Consts c, int p
 // other without a launch between them:
 //   - every workgroup keeps the schedule (clock, level histogram), the set of
 //     the finest particles (all those of a level of at least `floor`, at most
-//     cap of them) with their state in LDS, and the state of the j it owns in
-//     registers;
+//     cap of them) with their state in LDS, and the state of the other j it
+//     owns in registers;
 //   - a step: the set's particles due at the next block time are active; each
 //     workgroup computes their sums over its own j slices and publishes them;
 //   - every workgroup reads all published sums and corrects all active
 //     particles, so that the set, the histogram and the clock stay alike
-//     everywhere and one exchange per step is enough.
+//     everywhere and one exchange per step is enough;
+//   - up to 1024 particles (kWhole) every workgroup owns them all, and a step of
+//     at most kTeamSolo active ones is computed in each, without an exchange.
 // The launch ends before a step that reaches below floor (it has other
 // particles), or has more than cap of them.
 // The sums are those of the one-particle decomposition in the same order, and
@@ -1305,10 +1309,15 @@ __global__ __launch_bounds__(kBlock) void k_step_correct(DevC d, Consts c, int p
 // one i predicts it in registers, eight lanes correct one particle, and
 // the workgroup synchronises three times a step.
 // Measured, one largest step (1/8 time unit) of a Plummer sphere, with the two
-// kernels alone -> with the team: N = 256 2.93 -> 1.63 ms, 1024 8.20 -> 5.26,
-// 4096 21.0 -> 14.5, 8192 31.2 -> 24.7, 16384 58.1 -> 52.6 ms. A step in a team
+// kernels alone -> with the team: N = 256 2.93 -> 1.26 ms, 1024 8.20 -> 4.84,
+// 4096 21.0 -> 14.0, 8192 31.2 -> 23.8, 16384 58.1 -> 51.1 ms. A step in a team
 // takes 6 to 7 us: the exchange 2, the sums 1.4, the correction 1.3, the
-// schedule and the prediction of the owned j 0.8.
+// schedule and the prediction of the owned j 0.7. The kernel is short of scalar
+// registers: kWhole as a variant of its own, and the owned state in registers
+// with the set's read from the set (it had a copy in LDS that every correction
+// wrote), are 2 to 4 % of each size. Whole owners (with steps that exchange
+// nothing): N = 256 1.62 -> 1.26 ms, 512 3.83 -> 3.18, 768 5.10 -> 4.65, 1024
+// 5.22 -> 4.84.
 //
 // The exchange. A sum travels as 16 bytes {low word, epoch, high word, epoch}
 // in a line of its own per (active particle, owner), written and read with
@@ -1371,11 +1380,23 @@ __device__ __forceinline__ bool team_agreed(int* word, int wgs, long long ticks)
 // What a workgroup of a team knows about its own j slices.
 struct TeamOwn {
   int w, grp;     // owner index, group
-  int slices;     // owned slices (1 or 2)
-  int slice[2];   // their numbers
+  int slices;     // owned slices (1 to 4)
+  int slice[2];   // their numbers (one owner of all: 0, 1, ...)
   int tps, len;   // tiles (1 or 2) and j per slice
   int lg_len;     // log2(len)
-  bool direct;    // one slice, in a team of several: its sums are published as they are
+};
+// kWhole: a team of whole owners, each of all slices.
+template <bool kWhole>
+__device__ __forceinline__ int own_slice(const TeamOwn& o, int k) {
+  return kWhole ? k : o.slice[k ? 1 : 0];
+}
+
+// How the workgroups share a step: group grp of g computes the active
+// particles grp, grp + g, ...; what becomes of a sum.
+struct TeamShare {
+  int grp, g, units;
+  bool local;   // the workgroup has every j and computes every particle: nothing is exchanged
+  bool direct;  // one slice: its sums are published as they are
 };
 
 // Slice stored in slot q of s (the inverse of slice_slot).
@@ -1383,19 +1404,27 @@ __device__ __forceinline__ int slot_slice(int q, int s) {
   return (s & 7) ? q : (q % (s >> 3)) * 8 + q / (s >> 3);
 }
 
-// Time from entry e's last correction to t_next: a particle of level k was
-// last corrected at a multiple of its step.
-__device__ __forceinline__ double team_dt(const TeamMem& s, const Consts& c, int e, long long t_now,
-                                          long long t_next) {
-  const int sh = c.kmax - s.lev[e];
+// Time from the last correction of a particle of level lev to t_next: it was
+// corrected at the last multiple of its step.
+__device__ __forceinline__ double team_dt(const Consts& c, int lev, long long t_now, long long t_next) {
+  const int sh = c.kmax - lev;
   return (double)(t_next - ((t_now >> sh) << sh)) * c.dt_min;
 }
 
 // Entry e predicted to t_next.
 __device__ __forceinline__ void team_predict(const TeamMem& s, const Consts& c, int e, long long t_now,
                                              long long t_next, double (&p)[6]) {
-  taylor6(team_dt(s, c, e, t_now, t_next), s.st[kX][e], s.st[kY][e], s.st[kZ][e], s.st[kVx][e], s.st[kVy][e],
+  taylor6(team_dt(c, s.lev[e], t_now, t_next), s.st[kX][e], s.st[kY][e], s.st[kZ][e], s.st[kVx][e], s.st[kVy][e],
           s.st[kVz][e], s.st[kAx][e], s.st[kAy][e], s.st[kAz][e], s.st[kJx][e], s.st[kJy][e], s.st[kJz][e], p);
+}
+
+// State and level of entry e.
+__device__ __forceinline__ void team_entry(const TeamMem& s, int e, PState& p) {
+  p.x = s.st[kX][e]; p.y = s.st[kY][e]; p.z = s.st[kZ][e];
+  p.vx = s.st[kVx][e]; p.vy = s.st[kVy][e]; p.vz = s.st[kVz][e];
+  p.ax = s.st[kAx][e]; p.ay = s.st[kAy][e]; p.az = s.st[kAz][e];
+  p.jx = s.st[kJx][e]; p.jy = s.st[kJy][e]; p.jz = s.st[kJz][e];
+  p.lev = s.lev[e];
 }
 
 // Publishes sum comp of active particle u (see the exchange above).
@@ -1408,18 +1437,18 @@ __device__ __forceinline__ void team_publish(const Team& t, const TeamOwn& o, __
 }
 
 // Sums of kI active particles over one owned slice, by one wave (lanes split
-// the j as k_force's do with 64 lanes per i): published if the workgroup owns
-// one slice, else psum[unit][slice][6]. bh: the central particle's entry.
-template <bool kMaskSelf, bool kCentral, bool kMixed, int kI>
+// the j as k_force's do with 64 lanes per i): published, or left in psum
+// (rows of ks per unit). bh: the central particle's entry.
+template <bool kMaskSelf, bool kCentral, bool kMixed, bool kWhole, int kI>
 __device__ __forceinline__ void team_item(const DevC& d, const Consts& c, const Team& t, const TeamOwn& o,
-                                          TeamMem& s, int unit, int units, int k, long long t_now,
+                                          const TeamShare& sh, TeamMem& s, int unit, int k, long long t_now,
                                           long long t_next, int bh, __amdgpu_buffer_rsrc_t lines,
                                           unsigned epoch) {
   const int lane = threadIdx.x & 63;
   ILane<kI> I;
 #pragma unroll
   for (int q = 0; q < kI; ++q) {
-    const int e = s.act[o.grp + min(unit * kI + q, units - 1) * t.g];
+    const int e = s.act[sh.grp + min(unit * kI + q, sh.units - 1) * sh.g];
     double p[6];
     team_predict(s, c, e, t_now, t_next, p);
     I.g[q] = (kMaskSelf || kCentral) ? s.idx[e] : 0;
@@ -1428,12 +1457,13 @@ __device__ __forceinline__ void team_item(const DevC& d, const Consts& c, const 
     I.vx[q] = p[3]; I.vy[q] = p[4]; I.vz[q] = p[5];
     I.A[q] = Acc6{0, 0, 0, 0, 0, 0};
   }
-  const int j0 = o.slice[k] * o.len, j1 = min(c.n, j0 + o.len);
+  const int slice = own_slice<kWhole>(o, k);
+  const int j0 = slice * o.len, j1 = min(c.n, j0 + o.len);
   for (int tt = 0; tt < o.tps && j0 + tt * kTileJ < j1; ++tt) {
     const int jt = j0 + tt * kTileJ;
-    tile_pairs<kMaskSelf, kMixed, kI, true>(s.tile[k + tt], min(kTileJ, j1 - jt), 64, lane, jt, c.eps2, I);
+    tile_pairs<kMaskSelf, kMixed, kI, true>(s.tile[k * o.tps + tt], min(kTileJ, j1 - jt), 64, lane, jt, c.eps2, I);
   }
-  if (kCentral && o.slice[k] == 0 && lane == 0) {
+  if (kCentral && slice == 0 && lane == 0) {
     double b[6];
     team_predict(s, c, bh, t_now, t_next, b);
     const double bm = d.m[c.bh];
@@ -1465,16 +1495,33 @@ __device__ __forceinline__ void team_item(const DevC& d, const Consts& c, const 
   constexpr int kPart = kI == 2 ? 16 : 32;
   if ((lane & (kPart - 1)) == 0) {
     const int u = unit * kI + (kI == 2 ? lane >> 5 : 0), comp = (lane & kPart) ? 3 : 0;
-    if (u < units) {
-      if (o.direct) {
+    if (u < sh.units) {
+      if (sh.direct) {
 #pragma unroll
-        for (int q = 0; q < 3; ++q) team_publish(t, o, lines, epoch, o.grp + u * t.g, comp + q, 0.0 + r[q]);
+        for (int q = 0; q < 3; ++q) team_publish(t, o, lines, epoch, sh.grp + u * sh.g, comp + q, 0.0 + r[q]);
       } else {
-        double* p = s.psum[u][k] + comp;
+        double* p = s.psum[u * t.ks + k] + comp;
         p[0] = r[0]; p[1] = r[1]; p[2] = r[2];
       }
     }
   }
+}
+
+// Component comp of unit u's sums over the owned slices, in the reduction's
+// order (of an owner's two slots, or of all four: 0 + 2, then 1 + 3).
+template <bool kWhole>
+__device__ __forceinline__ double team_slices(const Team& t, const TeamOwn& o, const TeamMem& s, int u, int comp) {
+  const double(*const p)[6] = s.psum + u * t.ks;
+  double f = 0.0 + p[0][comp];
+  if (kWhole && t.ks == 4) {
+    f += 0.0 + p[2][comp];
+    double g = 0.0 + p[1][comp];
+    if (o.slices == 4) g += 0.0 + p[3][comp];
+    f += g;
+  } else if (o.slices == 2) {
+    f += 0.0 + p[1][comp];
+  }
+  return f;
 }
 
 // Reads the published sums of the entries of this wave (e = wave, wave +
@@ -1598,7 +1645,7 @@ __device__ __forceinline__ double team_correct(const Consts& c, long long t_next
 // Small block steps of one cluster by workgroup me of its team. par >= 0: a
 // context's team, which leaves the list of parity par and the j stream
 // prepared for the next step; par < 0: a pool's, whose predictor does that.
-template <bool kMaskSelf, bool kCentral, bool kMixed>
+template <bool kMaskSelf, bool kCentral, bool kMixed, bool kWhole>
 __device__ __forceinline__ void team_body(const DevC& d, const Consts& c, const Team& t, int me, int max_steps,
                                           int par) {
   extern __shared__ __align__(16) char smem[];
@@ -1627,32 +1674,33 @@ __device__ __forceinline__ void team_body(const DevC& d, const Consts& c, const 
   o.tps = ((n + kTileJ - 1) / kTileJ + c.s1 - 1) / c.s1;
   o.len = o.tps * kTileJ;
   o.lg_len = o.tps == 2 ? 9 : 8;
-  o.direct = t.ks == 1 && t.wgs > 1;
-  o.slices = t.ks == 2 && o.w + t.width < c.s1 ? 2 : 1;
+  o.slices = kWhole ? c.s1 : t.ks == 2 && o.w + t.width < c.s1 ? 2 : 1;
   o.slice[0] = slot_slice(o.w, c.s1);
   o.slice[1] = o.slices == 2 ? slot_slice(o.w + t.width, c.s1) : 0;
   const long long sn = d.sn;
 
-  // The owned j of this thread: place tid % 256 of tile tid / 256 (of the slice,
-  // or of the second slice).
-  const int ot = tid / kTileJ, ok = tid % kTileJ;
-  int j = -1;
-  {
-    const int sl = t.ks == 2 ? ot : 0;
-    if (sl < o.slices && (t.ks == 2 || ot < o.tps)) {
-      const int j0 = o.slice[sl] * o.len;
-      const int jj = j0 + (t.ks == 2 ? 0 : ot * kTileJ) + ok;
-      if (jj < min(n, j0 + o.len)) j = jj;
-    }
-  }
-  {
-    const PState ps = load_pstate(d, max(j, 0));
-    const double st[12] = {ps.x, ps.y, ps.z, ps.vx, ps.vy, ps.vz, ps.ax, ps.ay, ps.az, ps.jx, ps.jy, ps.jz};
+  // The owned j of this thread: places tid and, with more than two tiles, tid +
+  // 512; place p is in tile p / 256 of the owned slices', one after the other. Their state as the launch finds it: those of the set
+  // change, and are then read from the set (mem: their entries).
+  constexpr int kOwn = kWhole ? kTeamTiles * kTileJ / kTeamBlock : 1;
+  const int owns = t.ks * o.tps > kTeamBlock / kTileJ ? kOwn : 1;
+  int j[kOwn], mem[kOwn];
+  PState own[kOwn];
 #pragma unroll
-    for (int q = 0; q < 12; ++q) s.own[q][tid] = st[q];
-    s.tick[tid] = ps.tick;
-    s.olev[tid] = ps.lev;
-    s.tile[ot][6][ok] = (kCentral ? d.jm : d.m)[max(j, 0)];
+  for (int z = 0; z < kOwn; ++z) {
+    const int ot = (z * kTeamBlock + tid) / kTileJ, ok = tid % kTileJ;
+    j[z] = mem[z] = -1;
+    own[z] = PState{};
+    if (z >= owns) continue;
+    const int sl = o.tps == 2 ? ot >> 1 : ot;
+    if (sl < o.slices) {
+      const int j0 = own_slice<kWhole>(o, sl) * o.len;
+      const int jj = j0 + (ot - sl * o.tps) * kTileJ + ok;
+      if (jj < min(n, j0 + o.len)) j[z] = jj;
+    }
+    own[z] = load_pstate(d, max(j[z], 0));
+    s.tile[ot][6][ok] = (kCentral ? d.jm : d.m)[max(j[z], 0)];
+    s.mem[z * kTeamBlock + tid] = -1;
   }
   if (tid < 64) s.hist[tid] = tid <= kmax ? sc->hist[tid] : 0;
   if (tid == 0) {
@@ -1735,6 +1783,14 @@ __device__ __forceinline__ void team_body(const DevC& d, const Consts& c, const 
     }
     if (kCentral && tid == 0) s.lev[t.cap] = d.lev[c.bh];
     team_sync();
+    if (tid < n_ent) {
+      const int i = s.idx[tid];
+      const int slot = slice_slot((int)((unsigned)i >> o.lg_len), c.s1);
+      if ((slot & (t.width - 1)) == o.w) {
+        const int k = kWhole ? slot : slot >= t.width;
+        s.mem[i - (own_slice<kWhole>(o, k) - k) * o.len] = (short)tid;
+      }
+    }
     const int q = tid & 15;
     constexpr int kRows = kTeamBlock / 16;  // entries fetched together
     for (int e0 = tid >> 4; e0 < n_ent + (kCentral ? 1 : 0); e0 += 4 * kRows) {
@@ -1753,6 +1809,9 @@ __device__ __forceinline__ void team_body(const DevC& d, const Consts& c, const 
     }
     team_sync();
   }
+#pragma unroll
+  for (int z = 0; z < kOwn; ++z)
+    if (z < owns) mem[z] = s.mem[z * kTeamBlock + tid];
 
   long long psteps = 0, t_next = 0;
   int steps = 0, kthr = 0;
@@ -1770,7 +1829,6 @@ __device__ __forceinline__ void team_body(const DevC& d, const Consts& c, const 
     kthr = max(0, kmax - (int)__builtin_ctzll((unsigned long long)t_next));
     done = t_next > t_end;
     if (done || steps >= max_steps || bad || kthr < floor_lev) break;
-    ++epoch;
     // The active entries, counted by every wave.
     int n_act = 0;
 #pragma unroll
@@ -1781,46 +1839,47 @@ __device__ __forceinline__ void team_body(const DevC& d, const Consts& c, const 
       n_act += __popcll(m);
     }
     // The owned j predicted to t_next.
-    {
-      double p[6];
-      taylor6((double)(t_next - s.tick[tid]) * c.dt_min, s.own[kX][tid], s.own[kY][tid], s.own[kZ][tid],
-              s.own[kVx][tid], s.own[kVy][tid], s.own[kVz][tid], s.own[kAx][tid], s.own[kAy][tid],
-              s.own[kAz][tid], s.own[kJx][tid], s.own[kJy][tid], s.own[kJz][tid], p);
 #pragma unroll
-      for (int q = 0; q < 6; ++q) s.tile[ot][q][ok] = p[q];
+    for (int z = 0; z < kOwn; ++z) {
+      if (z >= owns) continue;
+      PState ps = own[z];
+      if (mem[z] >= 0) team_entry(s, mem[z], ps);
+      double p[6];
+      taylor6(team_dt(c, ps.lev, t_now, t_next), ps.x, ps.y, ps.z, ps.vx, ps.vy, ps.vz, ps.ax, ps.ay, ps.az, ps.jx, ps.jy, ps.jz, p);
+#pragma unroll
+      for (int q = 0; q < 6; ++q) s.tile[(z * kTeamBlock + tid) / kTileJ][q][tid % kTileJ] = p[q];
     }
     team_sync();
     // Sums over the owned slices: one particle per wave and item while that
     // keeps waves busy, else two.
-    const int units = n_act > o.grp ? (n_act - o.grp + t.g - 1) / t.g : 0;
+    TeamShare sh;
+    sh.local = t.wgs == 1 || (kWhole && n_act <= kTeamSolo);
+    sh.direct = t.ks == 1 && !sh.local;
+    sh.grp = sh.local ? 0 : o.grp;
+    sh.g = sh.local ? 1 : t.g;
+    sh.units = sh.local ? n_act : n_act > sh.grp ? (n_act - sh.grp + sh.g - 1) / sh.g : 0;
+    epoch += !sh.local;
+    const int units = sh.units;
     const int bh = kCentral ? s.bh : 0;
     if (units * o.slices <= kTeamWaves) {
       if (wave < units * o.slices)
-        team_item<kMaskSelf, kCentral, kMixed, 1>(d, c, t, o, s, wave / o.slices, units, wave % o.slices, t_now,
+        team_item<kMaskSelf, kCentral, kMixed, kWhole, 1>(d, c, t, o, sh, s, wave / o.slices, wave % o.slices, t_now,
                                                   t_next, bh, lines, epoch);
     } else {
       for (int it = wave; it < (units + 1) / 2 * o.slices; it += kTeamWaves)
-        team_item<kMaskSelf, kCentral, kMixed, 2>(d, c, t, o, s, it / o.slices, units, it % o.slices, t_now,
+        team_item<kMaskSelf, kCentral, kMixed, kWhole, 2>(d, c, t, o, sh, s, it / o.slices, it % o.slices, t_now,
                                                   t_next, bh, lines, epoch);
     }
-    // Sums of two slices, added first; and a group without a particle publishes
-    // an empty entry, so that every workgroup is waited for in every exchange.
     team_sync();  // (no wave still reads the set when another corrects it)
-    if (!o.direct || units == 0)
-      for (int x = tid; x < max(units, 1) * 8; x += kTeamBlock) {
-        const int u = x >> 3, comp = x & 7, e = o.grp + u * t.g;
-        if (comp >= 6) continue;
-        double f = 0.0;
-        if (units) {
-          f = 0.0 + s.psum[u][0][comp];
-          if (o.slices == 2) f += 0.0 + s.psum[u][1][comp];
+    if (!sh.local) {
+      // Sums of several slices; and a group without a particle publishes an
+      // empty entry, so that every workgroup is waited for in every exchange.
+      if (!sh.direct || units == 0)
+        for (int x = tid; x < max(units, 1) * 8; x += kTeamBlock) {
+          const int u = x >> 3, comp = x & 7;
+          if (comp < 6)
+            team_publish(t, o, lines, epoch, sh.grp + u * sh.g, comp, units ? team_slices<kWhole>(t, o, s, u, comp) : 0.0);
         }
-        if (t.wgs > 1) team_publish(t, o, lines, epoch, e, comp, f);
-        else if (units) s.ftot[comp][e] = f;
-      }
-    if (t.wgs == 1) {
-      team_sync();
-    } else {
       bool fine;
       if (t.width > 32) fine = team_collect<8>(t, lines, epoch, n_act, s);
       else if (t.width > 16) fine = team_collect<4>(t, lines, epoch, n_act, s);
@@ -1831,46 +1890,38 @@ __device__ __forceinline__ void team_body(const DevC& d, const Consts& c, const 
       __builtin_amdgcn_wave_barrier();
     }
     // Correction: 8 lanes per particle, of the wave that collected its sums.
-    for (int u0 = wave; u0 < n_act; u0 += 64) {
-      const int u = u0 + kTeamWaves * (lane >> 3);
-      const bool in = u < n_act;
-      const int uu = in ? u : u0, e = s.act[uu];
-      const int r = lane & 7, q = min(r & 3, 2);
-      const bool vel = r >= 4;
-      const int lv = s.lev[e];
-      const double fa = s.ftot[q][uu], fj = s.ftot[3 + q][uu];
-      int nl;
-      bool clamped;
-      const double out = team_correct(c, t_next, lv, vel, s.st[q][e], s.st[3 + q][e], s.st[6 + q][e], s.st[9 + q][e],
-                                      fa, fj, nl, clamped);
-      __builtin_amdgcn_wave_barrier();  // (every lane has read the entry)
-      if (!in || (r & 3) == 3) continue;
-      const double f = vel ? fj : fa;
-      s.st[(vel ? 3 : 0) + q][e] = out;
-      s.st[(vel ? 9 : 6) + q][e] = f;
-      if (!isfinite(f)) s.bad = 1;
-      const int i = s.idx[e];
-      const int slot = slice_slot((int)((unsigned)i >> o.lg_len), c.s1);
-      const bool mine = (slot & (t.width - 1)) == o.w;
-      const bool second = t.ks == 2 && slot >= t.width;
-      const int place = i - o.slice[second ? 1 : 0] * o.len + (second ? kTileJ : 0);
-      if (mine) {
-        s.own[(vel ? 3 : 0) + q][place] = out;
-        s.own[(vel ? 9 : 6) + q][place] = f;
-      }
-      if (r == 0) {
-        if (clamped) atomicAdd(&s.clamp, 1);
-        if (nl != lv) {
-          s.lev[e] = nl;
-          atomicAdd(&s.hist[lv], -1);
-          atomicAdd(&s.hist[nl], 1);
-        }
-        if (mine) {
-          s.tick[place] = t_next;
-          s.olev[place] = nl;
+    auto correct = [&](auto local) {
+      for (int u0 = wave; u0 < n_act; u0 += 64) {
+        const int u = u0 + kTeamWaves * (lane >> 3);
+        const bool in = u < n_act;
+        const int uu = in ? u : u0, e = s.act[uu];
+        const int r = lane & 7, q = min(r & 3, 2);
+        const bool vel = r >= 4;
+        const int lv = s.lev[e];
+        const double fa = decltype(local)::value ? team_slices<kWhole>(t, o, s, uu, q) : s.ftot[q][uu];
+        const double fj = decltype(local)::value ? team_slices<kWhole>(t, o, s, uu, 3 + q) : s.ftot[3 + q][uu];
+        int nl;
+        bool clamped;
+        const double out = team_correct(c, t_next, lv, vel, s.st[q][e], s.st[3 + q][e], s.st[6 + q][e], s.st[9 + q][e],
+                                        fa, fj, nl, clamped);
+        __builtin_amdgcn_wave_barrier();  // (every lane has read the entry)
+        if (!in || (r & 3) == 3) continue;
+        const double f = vel ? fj : fa;
+        s.st[(vel ? 3 : 0) + q][e] = out;
+        s.st[(vel ? 9 : 6) + q][e] = f;
+        if (!isfinite(f)) s.bad = 1;
+        if (r == 0) {
+          if (clamped) atomicAdd(&s.clamp, 1);
+          if (nl != lv) {
+            s.lev[e] = nl;
+            atomicAdd(&s.hist[lv], -1);
+            atomicAdd(&s.hist[nl], 1);
+          }
         }
       }
-    }
+    };
+    if (sh.local) correct(std::true_type{});
+    else correct(std::false_type{});
     team_sync();
     bin += lane == 31 - __clz(n_act);
     psteps += n_act;
@@ -1899,28 +1950,29 @@ __device__ __forceinline__ void team_body(const DevC& d, const Consts& c, const 
   // The corrected particles of the owned slices; the next step's list and j
   // stream; the record.
   if (o.grp == 0) {
-    PState ps{};
-    bool take = false;
-    double p[6];
-    if (j >= 0) {
-      ps.x = s.own[kX][tid]; ps.y = s.own[kY][tid]; ps.z = s.own[kZ][tid];
-      ps.vx = s.own[kVx][tid]; ps.vy = s.own[kVy][tid]; ps.vz = s.own[kVz][tid];
-      ps.ax = s.own[kAx][tid]; ps.ay = s.own[kAy][tid]; ps.az = s.own[kAz][tid];
-      ps.jx = s.own[kJx][tid]; ps.jy = s.own[kJy][tid]; ps.jz = s.own[kJz][tid];
-      ps.tick = s.tick[tid];
-      ps.lev = s.olev[tid];
-      if (ps.tick > t_start) {
-        st_arr(d, kX)[j] = ps.x; st_arr(d, kY)[j] = ps.y; st_arr(d, kZ)[j] = ps.z;
-        st_arr(d, kVx)[j] = ps.vx; st_arr(d, kVy)[j] = ps.vy; st_arr(d, kVz)[j] = ps.vz;
-        st_arr(d, kAx)[j] = ps.ax; st_arr(d, kAy)[j] = ps.ay; st_arr(d, kAz)[j] = ps.az;
-        st_arr(d, kJx)[j] = ps.jx; st_arr(d, kJy)[j] = ps.jy; st_arr(d, kJz)[j] = ps.jz;
-        d.tick[j] = ps.tick;
-        d.lev[j] = (unsigned char)ps.lev;
+#pragma unroll
+    for (int z = 0; z < kOwn; ++z) {
+      if (z >= owns) continue;
+      PState ps = own[z];
+      const int i = j[z];
+      if (mem[z] >= 0) team_entry(s, mem[z], ps);
+      const int sh = kmax - ps.lev;
+      ps.tick = (t_now >> sh) << sh;
+      if (mem[z] >= 0) {
+        if (ps.tick > t_start) {
+          st_arr(d, kX)[i] = ps.x; st_arr(d, kY)[i] = ps.y; st_arr(d, kZ)[i] = ps.z;
+          st_arr(d, kVx)[i] = ps.vx; st_arr(d, kVy)[i] = ps.vy; st_arr(d, kVz)[i] = ps.vz;
+          st_arr(d, kAx)[i] = ps.ax; st_arr(d, kAy)[i] = ps.ay; st_arr(d, kAz)[i] = ps.az;
+          st_arr(d, kJx)[i] = ps.jx; st_arr(d, kJy)[i] = ps.jy; st_arr(d, kJz)[i] = ps.jz;
+          d.tick[i] = ps.tick;
+          d.lev[i] = (unsigned char)ps.lev;
+        }
       }
-    }
-    if (par >= 0 && !done && !s.bad) {
-      if (j >= 0) {
-        predict_store(d, j, (double)(t_next - ps.tick) * c.dt_min, ps, p);
+      if (par < 0 || done || s.bad) continue;
+      bool take = false;
+      double p[6];
+      if (i >= 0) {
+        predict_store(d, i, (double)(t_next - ps.tick) * c.dt_min, ps, p);
         take = ps.lev >= kthr;
       }
       const unsigned long long ball = __ballot(take);
@@ -1928,7 +1980,7 @@ __device__ __forceinline__ void team_body(const DevC& d, const Consts& c, const 
       if (lane == 0 && ball) base = atomicAdd(&sc->lcnt[par], __popcll(ball));
       base = __builtin_amdgcn_readfirstlane(base);
       if (take)
-        list_store(d, n, par, base + __popcll(ball & ((1ULL << lane) - 1ULL)), j, p, ps.ax, ps.ay, ps.az, ps.jx,
+        list_store(d, n, par, base + __popcll(ball & ((1ULL << lane) - 1ULL)), i, p, ps.ax, ps.ay, ps.az, ps.jx,
                    ps.jy, ps.jz, ps.lev, t_next);
     }
   }
@@ -1948,9 +2000,9 @@ __device__ __forceinline__ void team_body(const DevC& d, const Consts& c, const 
   }
 }
 
-template <bool kMaskSelf, bool kCentral, bool kMixed>
+template <bool kMaskSelf, bool kCentral, bool kMixed, bool kWhole>
 __global__ __launch_bounds__(kTeamBlock) void k_team(DevC d, Consts c, Team t, int par) {
-  team_body<kMaskSelf, kCentral, kMixed>(d, c, t, blockIdx.x, kTeamSteps, par);
+  team_body<kMaskSelf, kCentral, kMixed, kWhole>(d, c, t, blockIdx.x, kTeamSteps, par);
 }
 
 __global__ void k_team_clear(Sched* __restrict__ sc, uint4* __restrict__ lines, int words) {
@@ -2809,7 +2861,7 @@ __global__ __launch_bounds__(kTeamBlock) void k_pool_team(const PoolSlot* __rest
   const PoolItem it = pool_item(s_off, tab->order, nullptr, count, blockIdx.x);
   const PoolSlot& ps = slots[it.slot];
   const DevC d = compact_view(ps.d);
-  team_body<false, false, kMixed>(d, ps.c, ps.t, it.blk, kPoolTeamSteps, -1);
+  team_body<false, false, kMixed, false>(d, ps.c, ps.t, it.blk, kPoolTeamSteps, -1);
 }
 
 template <bool kMixed>
@@ -3319,11 +3371,17 @@ hipError_t launch_step_correct(const Dev& d, const Consts& c, int par, hipStream
   return hipGetLastError();
 }
 
+template <bool kWhole>
+static auto team_kernel(const Consts& c) {
+  return c.mixed ? (c.bh >= 0 ? k_team<false, true, true, kWhole>
+                              : (c.eps2 > 0.0 ? k_team<false, false, true, kWhole> : k_team<true, false, true, kWhole>))
+                 : (c.bh >= 0 ? k_team<false, true, false, kWhole>
+                              : (c.eps2 > 0.0 ? k_team<false, false, false, kWhole>
+                                              : k_team<true, false, false, kWhole>));
+}
+
 hipError_t launch_team(const Dev& d, const Consts& c, const Team& t, int par, hipStream_t s) {
-  auto kern = c.mixed ? (c.bh >= 0 ? k_team<false, true, true>
-                                   : (c.eps2 > 0.0 ? k_team<false, false, true> : k_team<true, false, true>))
-                      : (c.bh >= 0 ? k_team<false, true, false>
-                                   : (c.eps2 > 0.0 ? k_team<false, false, false> : k_team<true, false, false>));
+  auto kern = t.wp == 1 ? team_kernel<true>(c) : team_kernel<false>(c);
   hipLaunchKernelGGL(kern, dim3(t.wgs), dim3(kTeamBlock), sizeof(TeamMem), s, compact_view(d), c, t, par);
   return hipGetLastError();
 }
