@@ -286,6 +286,24 @@ void report_progress(gd_ctx* c) {
   std::fflush(stderr);
 }
 
+}  // namespace
+
+// The schedule record copied, word by word, to pinned host memory: the last
+// node of a replayed graph, so that the host reads a replay's status without
+// a separate copy; and the last kernel of an admission to a pool.
+static_assert(sizeof(Sched) % 8 == 0, "the status copy moves whole 8-byte words");
+__global__ void k_status_out(const unsigned long long* __restrict__ sc, unsigned long long* __restrict__ out) {
+  for (int k = threadIdx.x; k < kSchedWords; k += blockDim.x) out[k] = sc[k];
+  __threadfence_system();
+}
+
+namespace {
+
+hipError_t launch_status_out(const Sched* sc, Sched* out, hipStream_t s) {
+  hipLaunchKernelGGL(k_status_out, dim3(1), dim3(64), 0, s, (const unsigned long long*)sc, (unsigned long long*)out);
+  return hipGetLastError();
+}
+
 gd_status read_sched(gd_ctx* c) {
   GD_TRY(c->hip(hipMemcpyAsync(c->h_sc, c->d.sc, sizeof(Sched), hipMemcpyDeviceToHost, c->stream),
                 "read status"));
@@ -310,19 +328,6 @@ gd_status enqueue_step(gd_ctx* c, hipStream_t s, int par, hipEvent_t ev_s, hipEv
 }
 
 // Captures kGraphSteps block steps into *out.
-}  // namespace
-
-// The schedule record copied, word by word, to pinned host memory: the last
-// node of a replayed graph, so that the host reads a replay's status without
-// a separate copy.
-static_assert(sizeof(Sched) % 8 == 0, "the status copy moves whole 8-byte words");
-__global__ void k_status_out(const unsigned long long* __restrict__ sc, unsigned long long* __restrict__ out) {
-  for (int k = threadIdx.x; k < kSchedWords; k += blockDim.x) out[k] = sc[k];
-  __threadfence_system();
-}
-
-namespace {
-
 gd_status build_graph(gd_ctx* c, int ring) {
   hipGraphExec_t* out = &c->graph[ring];
   if (*out) return GD_OK;
@@ -336,11 +341,7 @@ gd_status build_graph(gd_ctx* c, int ring) {
     if (c->team.wgs) st = c->hip(launch_team(c->d, c->c, c->team, k & 1, c->capture_stream), "team kernel");
     if (st == GD_OK) st = enqueue_step(c, c->capture_stream, k & 1, nullptr, nullptr);
   }
-  if (st == GD_OK) {
-    hipLaunchKernelGGL(k_status_out, dim3(1), dim3(64), 0, c->capture_stream,
-                       (const unsigned long long*)c->d.sc, (unsigned long long*)c->h_ring[ring]);
-    st = c->hip(hipGetLastError(), "status kernel");
-  }
+  if (st == GD_OK) st = c->hip(launch_status_out(c->d.sc, c->h_ring[ring], c->capture_stream), "status kernel");
   hipError_t e = hipStreamEndCapture(c->capture_stream, &g);
   if (st != GD_OK) {
     if (g) (void)hipGraphDestroy(g);
@@ -361,12 +362,12 @@ gd_status initialise(gd_ctx* c, const double* m, const double* x, const double* 
   GD_TRY(c->hip(launch_load(d, c->c, m, x, v, c->stream), "load kernel"));
   GD_TRY(c->hip(launch_predict(d, c->c, kPredAll, 0.0, c->stream), "predict kernel"));
   const hipEvent_t ev_s = c->prof ? c->ev_s[kGraphSteps] : nullptr, ev_e = c->prof ? c->ev_e[kGraphSteps] : nullptr;
-  const bool sym = sym_init(c->c);
-  if (sym) {
+  if (sym_init(c->c)) {
     GD_TRY(c->hip(launch_sym_init(d, c->c, make_sym_plan(c->c), c->h_e, c->stream, ev_s, ev_e), "initial force"));
   } else {
     GD_TRY(c->hip(launch_force(d, c->c, c->stream, ev_s, ev_e), "force kernel"));
     GD_TRY(c->hip(launch_init_dt(d, c->c, c->stream), "init dt kernel"));
+    GD_TRY(c->hip(launch_energy(d, c->c, 0, c->h_e, c->stream), "energy kernel"));
   }
   GD_TRY(read_sched(c));
   if (c->h_sc->bad_input) return c->fail(GD_EINVAL, "non-finite or negative input (m, x or v)");
@@ -382,9 +383,7 @@ gd_status initialise(gd_ctx* c, const double* m, const double* x, const double* 
     c->bucket_launches[b] += 1;
     c->bucket_pairs[b] += c->n * c->n;
   }
-  double e[3] = {c->h_e[0], c->h_e[1], 0.0};
-  if (!sym) GD_TRY(energy_now(c, 0, e));
-  c->e0 = c->e_last = e[0] + e[1];
+  c->e0 = c->e_last = c->h_e[0] + c->h_e[1];
   c->t_now = 0;
   c->wall_s = 0.0;
   c->synced = true;
@@ -1073,12 +1072,13 @@ struct gd_pool {
   size_t arena_bytes = 0, heap_off = 0;
   PoolSlot* d_slots = nullptr;
   PoolTable* d_tab = nullptr;
-  PoolStatus* d_status = nullptr;
   PoolWork* d_work = nullptr;
-  PoolStatus* h_status = nullptr;  // pinned
+  PoolStatus* h_status = nullptr;  // pinned; written by the replays
+  Sched* h_sc = nullptr;           // pinned: the record of a cluster that is admitted
   PoolTable* h_tab = nullptr;      // pinned staging
   PoolSlot* h_slot = nullptr;      // pinned staging
   double* h_e = nullptr;           // pinned energy result
+  bool staged = false;             // uploads from h_tab and h_slot may still run
   std::vector<PoolSlotHost> slots;
   std::string err;
 
@@ -1097,7 +1097,7 @@ namespace {
 
 size_t pool_table_bytes(int max_clusters) {
   return align_up(sizeof(PoolSlot) * (size_t)max_clusters) + align_up(sizeof(PoolTable)) +
-         align_up(sizeof(PoolStatus) * (size_t)max_clusters) + align_up(sizeof(PoolWork));
+         align_up(sizeof(PoolWork));
 }
 
 // First-fit placement of `bytes` in the arena heap, between the blocks of the
@@ -1118,7 +1118,15 @@ bool pool_place(gd_pool* P, size_t bytes, size_t* off) {
 }
 
 // Uploads the table of resident clusters (stream-ordered).
+// Waits for the stream.
+gd_status pool_sync(gd_pool* P) {
+  GD_TRY(P->hip(hipStreamSynchronize(P->stream), "synchronise"));
+  P->staged = false;
+  return GD_OK;
+}
+
 gd_status pool_upload_table(gd_pool* P) {
+  if (P->staged) GD_TRY(pool_sync(P));
   PoolTable& t = *P->h_tab;
   t.count = 0;
   int acc = 0, wgs = 0;
@@ -1138,15 +1146,14 @@ gd_status pool_upload_table(gd_pool* P) {
   t.pred_off[t.count] = acc;
   t.team_off[t.count] = wgs;
   P->teams = P->teams && wgs <= kPoolTeamWgs;
-  GD_TRY(P->hip(hipMemcpyAsync(P->d_tab, P->h_tab, sizeof(PoolTable), hipMemcpyHostToDevice, P->stream),
-                "upload pool table"));
-  // The staging buffer is reused by the next call: wait for the copy.
-  return P->hip(hipStreamSynchronize(P->stream), "synchronise");
+  P->staged = true;
+  return P->hip(hipMemcpyAsync(P->d_tab, P->h_tab, sizeof(PoolTable), hipMemcpyHostToDevice, P->stream),
+                "upload pool table");
 }
 
 gd_status pool_energy(gd_pool* P, PoolSlotHost& s, double* e) {
   GD_TRY(P->hip(launch_energy(s.d, s.c, 0, P->h_e, P->stream), "energy kernel"));
-  GD_TRY(P->hip(hipStreamSynchronize(P->stream), "synchronise"));
+  GD_TRY(pool_sync(P));
   *e = P->h_e[0] + P->h_e[1];
   return GD_OK;
 }
@@ -1164,7 +1171,7 @@ gd_status pool_build_graph(gd_pool* P, int teams) {
     if (teams) e = launch_pool_team(P->d_slots, P->d_tab, mixed, P->capture_stream);
     if (e == hipSuccess) e = launch_pool_step(P->d_slots, P->d_tab, P->d_work, mixed, P->capture_stream);
   }
-  if (e == hipSuccess) e = launch_pool_status(P->d_slots, P->d_tab, P->d_status, P->capture_stream);
+  if (e == hipSuccess) e = launch_pool_status(P->d_slots, P->d_tab, P->h_status, P->capture_stream);
   hipError_t e2 = hipStreamEndCapture(P->capture_stream, &g);
   if (e != hipSuccess || e2 != hipSuccess) {
     if (g) (void)hipGraphDestroy(g);
@@ -1221,13 +1228,12 @@ gd_status gd_pool_create(gd_pool** out, const gd_params* p, int32_t max_clusters
   off += align_up(sizeof(PoolSlot) * (size_t)max_clusters);
   P->d_tab = (PoolTable*)(P->arena + off);
   off += align_up(sizeof(PoolTable));
-  P->d_status = (PoolStatus*)(P->arena + off);
-  off += align_up(sizeof(PoolStatus) * (size_t)max_clusters);
   P->d_work = (PoolWork*)(P->arena + off);
   off += align_up(sizeof(PoolWork));
   P->heap_off = off;
   gd_status st = GD_OK;
   if (st == GD_OK) st = P->hip(hipHostMalloc((void**)&P->h_status, sizeof(PoolStatus) * max_clusters, 0), "pinned status");
+  if (st == GD_OK) st = P->hip(hipHostMalloc((void**)&P->h_sc, sizeof(Sched), 0), "pinned record");
   if (st == GD_OK) st = P->hip(hipHostMalloc((void**)&P->h_tab, sizeof(PoolTable), 0), "pinned table");
   if (st == GD_OK) st = P->hip(hipHostMalloc((void**)&P->h_slot, sizeof(PoolSlot), 0), "pinned slot");
   if (st == GD_OK) st = P->hip(hipHostMalloc((void**)&P->h_e, 4 * sizeof(double), 0), "pinned energy");
@@ -1285,24 +1291,20 @@ gd_status gd_pool_admit(gd_pool* P, int64_t n, const double* m, const double* x,
   if ((st = P->hip(launch_load(s.d, s.c, m, x, v, P->stream), "load kernel")) != GD_OK) return undo(st);
   if ((st = P->hip(launch_predict(s.d, s.c, kPredAll, 0.0, P->stream), "predict kernel")) != GD_OK)
     return undo(st);
-  const bool sym = sym_init(s.c);
-  if (sym) {
+  if (sym_init(s.c)) {
     if ((st = P->hip(launch_sym_init(s.d, s.c, make_sym_plan(s.c), P->h_e, P->stream), "initial force")) != GD_OK)
       return undo(st);
   } else {
     if ((st = P->hip(launch_force(s.d, s.c, P->stream), "force kernel")) != GD_OK) return undo(st);
     if ((st = P->hip(launch_init_dt(s.d, s.c, P->stream), "init dt kernel")) != GD_OK) return undo(st);
+    if ((st = P->hip(launch_energy(s.d, s.c, 0, P->h_e, P->stream), "energy kernel")) != GD_OK) return undo(st);
   }
   if ((st = P->hip(launch_set_tend(s.d, s.t_end, P->stream), "prepare")) != GD_OK) return undo(st);
-  Sched chk;
-  if ((st = P->hip(hipMemcpyAsync(&chk, s.d.sc, sizeof(Sched), hipMemcpyDeviceToHost, P->stream),
-                   "read status")) != GD_OK)
-    return undo(st);
-  if ((st = P->hip(hipStreamSynchronize(P->stream), "synchronise")) != GD_OK) return undo(st);
-  if (chk.bad_input) return undo(P->fail(GD_EINVAL, "non-finite or negative input (m, x or v)"));
-  if (chk.nonfinite) return undo(P->fail(GD_ENONFINITE, "non-finite initial acceleration or jerk"));
-  if (sym) s.e0 = P->h_e[0] + P->h_e[1];
-  else if ((st = pool_energy(P, s, &s.e0)) != GD_OK) return undo(st);
+  if ((st = P->hip(launch_status_out(s.d.sc, P->h_sc, P->stream), "read status")) != GD_OK) return undo(st);
+  if ((st = pool_sync(P)) != GD_OK) return undo(st);
+  if (P->h_sc->bad_input) return undo(P->fail(GD_EINVAL, "non-finite or negative input (m, x or v)"));
+  if (P->h_sc->nonfinite) return undo(P->fail(GD_ENONFINITE, "non-finite initial acceleration or jerk"));
+  s.e0 = P->h_e[0] + P->h_e[1];
   // Descriptor, then the table that makes the cluster resident.
   P->h_slot->d = s.d;
   P->h_slot->c = s.c;
@@ -1325,10 +1327,7 @@ gd_status gd_pool_run(gd_pool* P, int32_t* finished, int32_t* n_finished) {
   if (resident == 0) return GD_OK;
   GD_TRY(pool_build_graph(P, P->teams));
   GD_TRY(P->hip(hipGraphLaunch(P->graph[P->teams], P->stream), "pool graph launch"));
-  GD_TRY(P->hip(hipMemcpyAsync(P->h_status, P->d_status, sizeof(PoolStatus) * P->max_clusters,
-                               hipMemcpyDeviceToHost, P->stream),
-                "read pool status"));
-  GD_TRY(P->hip(hipStreamSynchronize(P->stream), "synchronise"));
+  GD_TRY(pool_sync(P));
   bool changed = false;
   for (int sl = 0; sl < P->max_clusters; ++sl) {
     PoolSlotHost& s = P->slots[sl];
@@ -1369,7 +1368,7 @@ gd_status gd_pool_result(gd_pool* P, int32_t sl, double* x, double* v, gd_stats*
     st->e = e;
     st->wall_s = std::chrono::duration<double>(s.t_done - s.t_admit).count();
   } else {
-    GD_TRY(P->hip(hipStreamSynchronize(P->stream), "synchronise"));
+    GD_TRY(pool_sync(P));
   }
   return GD_OK;
 }
@@ -1398,6 +1397,7 @@ void gd_pool_destroy(gd_pool* P) {
     if (g) (void)hipGraphExecDestroy(g);
   if (P->capture_stream) (void)hipStreamDestroy(P->capture_stream);
   if (P->h_status) (void)hipHostFree(P->h_status);
+  if (P->h_sc) (void)hipHostFree(P->h_sc);
   if (P->h_tab) (void)hipHostFree(P->h_tab);
   if (P->h_slot) (void)hipHostFree(P->h_slot);
   if (P->h_e) (void)hipHostFree(P->h_e);

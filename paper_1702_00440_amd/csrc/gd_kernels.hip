@@ -2934,6 +2934,7 @@ __global__ void k_pool_status(const PoolSlot* __restrict__ slots, const PoolTabl
   st.done = sc->done;
   st.nonfinite = sc->nonfinite;
   out[sl] = st;
+  __threadfence_system();
 }
 
 // ---------------------------------------------------------------------------
