@@ -149,7 +149,7 @@ def cpu_baseline(w, seconds):
 def full_force_imf(warmup, steps):
     """One O(N^2) force and jerk evaluation (N_act = N) of the mixed-precision
     workload's sphere (Plummer N = 262144, power-law IMF, eps 1e-4), in FP64
-    and in mixed precision: the force launch of gd_reinit timed with its own
+    and in mixed precision: the force launches of gd_reinit timed with their own
     HIP events (gd_profile_force), `steps` times after `warmup`; pair
     interactions per second, achieved FLOP/s at 60 flops per pair against
     the FP64 and FP32 vector peaks, and the largest per-particle relative
@@ -188,7 +188,10 @@ def full_force_imf(warmup, steps):
     out["mixed_vs_fp64_max_rel_diff"] = {"acc": _rel_rows(forces["mixed"][0], forces["fp64"][0]),
                                          "jerk": _rel_rows(forces["mixed"][1], forces["fp64"][1])}
     out["workload"] = "plummer_imf_n262144 full force (N_act = N = 262144), eps 1e-4, seed 5"
-    out["timing"] = "HIP events around each force launch (hipExtLaunchKernelGGL), average over launches"
+    out["timing"] = "HIP events from the start of a force evaluation's first launch to the end of its last, average"
+    out["note"] = ("pairs_per_s counts each (i, j) and (j, i); FP64 evaluates both, and the pair's potential, at once: "
+                   "44 FP64 issue slots instead of 70, so its achieved_tflops at 60 flops per ordered pair is a rate "
+                   "to compare by, not the unit's")
     return out
 
 

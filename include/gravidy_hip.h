@@ -372,7 +372,8 @@ gd_status gd_stats_get(gd_ctx* c, gd_stats* st);
 gd_status gd_nact_histogram(gd_ctx* c, int64_t* counts);
 
 /*
- * gd_step_to replays block steps of two kernels each: the force (with the
+ * gd_step_to replays block steps of two kernels each (runs of small steps, in
+ * contexts of up to 32512 particles, in one kernel): the force (with the
  * active set of the step) and the corrector, which also predicts every
  * particle to the next block time it expects (the next multiple of the
  * current smallest step) and lists the particles active then. When a

@@ -74,7 +74,7 @@ struct Plan {
 // Device-resident scheduling and bookkeeping record (lives in the workspace).
 //
 // Block steps replayed from a graph run two kernels each (k_step_force,
-// k_step_correct), and the step's parity (0/1, a kernel argument) picks one of
+// k_step_correct; small ones in a team, see k_team), and the step's parity (0/1, a kernel argument) picks one of
 // two active lists: the corrector of a step predicts every particle to the
 // speculated next block time and builds the next step's list in the other
 // list, and the next force kernel checks the speculation (see k_step_force).
