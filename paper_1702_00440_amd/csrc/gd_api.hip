@@ -92,8 +92,7 @@ Layout make_layout(long long n, int ipl) {
   L.nact_log = take(sizeof(int) * 72);
   // (contexts of a size that has teams hold kIPerLane i per lane; a pool's
   // team of the same cluster has fewer owners and groups)
-  const Team t = make_team((int)n, kIPerLane, (int)n, false);
-  L.xch = take(t.wgs ? team_line_bytes(t) : 0);
+  L.xch = take(team_room((int)n));
   L.total = off;
   return L;
 }
@@ -452,7 +451,7 @@ gd_status gd_init(gd_ctx** out, const gd_params* p, int64_t n, const double* m, 
       return cleanup_fail(st);
   }
 
-  if (c->team.wgs && (st = c->hip(launch_team_clear(d, c->team, c->stream), "team clear")) != GD_OK)
+  if (c->team.wgs && (st = c->hip(launch_team_clear(d, (int)c->n, c->stream), "team clear")) != GD_OK)
     return cleanup_fail(st);
   if ((st = initialise(c, m, x, v)) != GD_OK) return cleanup_fail(st);
   *out = c;
@@ -726,7 +725,7 @@ gd_status gd_step_to(gd_ctx* c, double t_end, gd_stats* st) {
   GD_TRY(read_sched(c));
   // (a team takes no step once its epochs are used up)
   if (c->team.wgs && c->h_sc->team_epoch >= kTeamLastEpoch / 2)
-    GD_TRY(c->hip(launch_team_clear(c->d, c->team, c->stream), "team clear"));
+    GD_TRY(c->hip(launch_team_clear(c->d, (int)c->n, c->stream), "team clear"));
   long long steps_before = c->h_sc->block_steps, pairs_before = c->h_sc->pairs;
   bool prepared = false;
   while (c->t_now < target) {
@@ -1065,9 +1064,9 @@ struct gd_pool {
   int max_clusters = 0;
   hipStream_t stream = nullptr;
   hipStream_t capture_stream = nullptr;
-  // The captured replays: without and with teams (kPoolRounds).
-  hipGraphExec_t graph[2] = {nullptr, nullptr};
-  bool teams = false;  // every resident cluster has a team, and they all fit
+  // The captured replays, without teams, with few and with many steps of the teams in a round.
+  hipGraphExec_t graph[3] = {};
+  int round = 0;  // the replay for the resident clusters: 0 without teams
   char* arena = nullptr;
   size_t arena_bytes = 0, heap_off = 0;
   PoolSlot* d_slots = nullptr;
@@ -1130,7 +1129,15 @@ gd_status pool_upload_table(gd_pool* P) {
   PoolTable& t = *P->h_tab;
   t.count = 0;
   int acc = 0, wgs = 0;
-  P->teams = true;
+  bool teams = true;  // every resident cluster has a team, and they all fit
+  // As many groups to each team as all of them have room for (kPoolTeamWgs).
+  int g = 1;
+  for (; g < kPoolTeamGroups; g *= 2) {
+    int all = 0;
+    for (const PoolSlotHost& s : P->slots)
+      if (s.resident && s.team.wgs) all += pool_team(s.team, (int)s.n, n1_of(s.c), 2 * g).wgs;
+    if (all > kPoolTeamWgs) break;
+  }
   for (int sl = 0; sl < P->max_clusters; ++sl) {
     const PoolSlotHost& s = P->slots[sl];
     if (!s.resident) continue;
@@ -1138,14 +1145,17 @@ gd_status pool_upload_table(gd_pool* P) {
     t.pred_off[t.count] = acc;
     t.team_off[t.count] = wgs;
     acc += (int)((s.n + kBlock - 1) / kBlock);
-    wgs += s.team.wgs;
+    const Team team = s.team.wgs ? pool_team(s.team, (int)s.n, n1_of(s.c), g) : s.team;
+    t.team_g[t.count] = team.g;
+    t.team_cap[t.count] = team.cap;
+    wgs += team.wgs;
     // (a cluster without a team would take one step per round)
-    P->teams = P->teams && s.team.wgs > 0;
+    teams = teams && s.team.wgs > 0;
     ++t.count;
   }
   t.pred_off[t.count] = acc;
   t.team_off[t.count] = wgs;
-  P->teams = P->teams && wgs <= kPoolTeamWgs;
+  P->round = !teams || wgs > kPoolTeamWgs ? 0 : g < kPoolWide ? 1 : 2;
   P->staged = true;
   return P->hip(hipMemcpyAsync(P->d_tab, P->h_tab, sizeof(PoolTable), hipMemcpyHostToDevice, P->stream),
                 "upload pool table");
@@ -1158,17 +1168,17 @@ gd_status pool_energy(gd_pool* P, PoolSlotHost& s, double* e) {
   return GD_OK;
 }
 
-gd_status pool_build_graph(gd_pool* P, int teams) {
-  if (P->graph[teams]) return GD_OK;
+gd_status pool_build_graph(gd_pool* P, int round) {
+  if (P->graph[round]) return GD_OK;
   const bool mixed = (P->p.flags & GD_FLAG_MIXED) != 0;
-  static_assert(kPoolRounds * (kPoolTeamSteps + 1) <= kPoolSteps, "a replay takes at most kPoolSteps steps");
-  const int rounds = teams ? kPoolRounds : kPoolSteps;
+  const int steps = round == 0 ? 0 : round == 1 ? kPoolTeamSteps : kPoolWideSteps;
+  const int rounds = kPoolSteps / (steps + 1);
   hipGraph_t g = nullptr;
   GD_TRY(P->hip(hipStreamBeginCapture(P->capture_stream, hipStreamCaptureModeThreadLocal),
                 "begin capture"));
   hipError_t e = hipSuccess;
   for (int k = 0; k < rounds && e == hipSuccess; ++k) {
-    if (teams) e = launch_pool_team(P->d_slots, P->d_tab, mixed, P->capture_stream);
+    if (steps) e = launch_pool_team(P->d_slots, P->d_tab, steps, mixed, P->capture_stream);
     if (e == hipSuccess) e = launch_pool_step(P->d_slots, P->d_tab, P->d_work, mixed, P->capture_stream);
   }
   if (e == hipSuccess) e = launch_pool_status(P->d_slots, P->d_tab, P->h_status, P->capture_stream);
@@ -1177,7 +1187,7 @@ gd_status pool_build_graph(gd_pool* P, int teams) {
     if (g) (void)hipGraphDestroy(g);
     return P->hip(e != hipSuccess ? e : e2, "capture pool graph");
   }
-  e = hipGraphInstantiate(&P->graph[teams], g, nullptr, nullptr, 0);
+  e = hipGraphInstantiate(&P->graph[round], g, nullptr, nullptr, 0);
   (void)hipGraphDestroy(g);
   return P->hip(e, "instantiate pool graph");
 }
@@ -1287,7 +1297,7 @@ gd_status gd_pool_admit(gd_pool* P, int64_t n, const double* m, const double* x,
   };
   gd_status st;
   if ((st = P->hip(launch_reset_sched(s.d, 0, P->stream), "reset")) != GD_OK) return undo(st);
-  if (s.team.wgs && (st = P->hip(launch_team_clear(s.d, s.team, P->stream), "team clear")) != GD_OK) return undo(st);
+  if (s.team.wgs && (st = P->hip(launch_team_clear(s.d, (int)n, P->stream), "team clear")) != GD_OK) return undo(st);
   if ((st = P->hip(launch_load(s.d, s.c, m, x, v, P->stream), "load kernel")) != GD_OK) return undo(st);
   if ((st = P->hip(launch_predict(s.d, s.c, kPredAll, 0.0, P->stream), "predict kernel")) != GD_OK)
     return undo(st);
@@ -1325,8 +1335,8 @@ gd_status gd_pool_run(gd_pool* P, int32_t* finished, int32_t* n_finished) {
   int resident = 0;
   for (const auto& s : P->slots) resident += s.resident;
   if (resident == 0) return GD_OK;
-  GD_TRY(pool_build_graph(P, P->teams));
-  GD_TRY(P->hip(hipGraphLaunch(P->graph[P->teams], P->stream), "pool graph launch"));
+  GD_TRY(pool_build_graph(P, P->round));
+  GD_TRY(P->hip(hipGraphLaunch(P->graph[P->round], P->stream), "pool graph launch"));
   GD_TRY(pool_sync(P));
   bool changed = false;
   for (int sl = 0; sl < P->max_clusters; ++sl) {

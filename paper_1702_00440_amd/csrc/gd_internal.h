@@ -420,6 +420,20 @@ inline long long sym_launch_end(const SymPlan& p, long long f) {
   return std::min(std::min(f + chunk, (f / p.nb + p.span) * p.nb), p.items);
 }
 
+// Bytes of exchange lines in a cluster's workspace: those of its context's team.
+inline size_t team_room(int n) {
+  const Team t = make_team(n, kIPerLane, n, false);
+  return t.wgs ? team_line_bytes(t) : 0;
+}
+// A pool's team t of n particles with g groups.
+inline Team pool_team(Team t, int n, int n1, int g) {
+  if (t.wp == 1) return t;  // (its steps need no exchange)
+  t.g = g;
+  t.wgs = t.wp * g;
+  t.cap = std::min({(t.wgs << 14) / n, kTeamMaxCap, n1, (int)(team_room(n) / ((size_t)2 * t.wp * kTeamLine))});
+  return t;
+}
+
 // Launch sizes for a context of n particles: enough workgroups for the
 // largest force decomposition and corrector layout over all block sizes
 // (sampled), capped; kernels loop over anything beyond the grid.
@@ -454,22 +468,31 @@ struct PoolSlot {
   Team t;
 };
 
-// With teams, a replay of a pool takes kPoolRounds times up to kPoolTeamSteps
-// steps in the teams and one of every cluster's in the packed launches. All
-// teams have to fit the chip (one workgroup per compute unit, by their LDS).
-// 48 clusters of 256 to 8192 to t = 1/8 took 87.9 ms without teams, 79.6 with
-// 8 x (3 + 1) steps, 84.2 with 4 x (7 + 1) and 90.9 with 16 x (1 + 1); 5
-// clusters 39.5, 33.2, 36.4 and 41.4 ms. (Rounds of a power of two of steps:
-// the clusters' large blocks then fall into the packed launches together.)
-constexpr int kPoolRounds = 8;
+// With teams, a replay of a pool is rounds of up to kPoolTeamSteps (or
+// kPoolWideSteps) steps in the teams and one of every cluster's in the packed
+// launches. All teams have to fit the chip (one workgroup per compute unit, by
+// their LDS), and get as many groups as they have room for: with more of them a
+// team takes larger steps, and fewer wait for the packed ones. 48 clusters of
+// 256 to 8192 to t = 1/8 (one group for most of the time) took 87.9 ms without
+// teams, 79.6 with 8 x (3 + 1) steps, 84.2 with 4 x (7 + 1) and 90.9 with
+// 16 x (1 + 1). With more groups: 5 clusters of up to 8192 32.2 ms with one,
+// 29.7 with four, 25.6 with 4 x (7 + 1) steps as well and 23.7 with 2 x
+// (15 + 1); 24 of up to 4096 31.9, 29.7, 26.8 and 28.4; 12 of up to 8192 46.3,
+// -, 37.6 and 40.8. (Rounds of a power of two of steps: the clusters' large
+// blocks then fall into the packed launches together.)
 constexpr int kPoolTeamSteps = 3;
+constexpr int kPoolWideSteps = 7;  // with at least kPoolWide groups to a team (2: 24 of up to 8192 51.3 ms, 4: 48.5)
+constexpr int kPoolWide = 4;
 constexpr int kPoolTeamWgs = 256;
+constexpr int kPoolTeamGroups = 8;
 
 struct PoolTable {
   int count;                   // resident clusters
   int order[kMaxPool];         // slot index of each resident cluster
   int pred_off[kMaxPool + 1];  // prefix sum of the clusters' predictor blocks
   int team_off[kMaxPool + 1];  // prefix sum of the teams' workgroups
+  int team_g[kMaxPool];        // their groups and largest steps (pool_team)
+  int team_cap[kMaxPool];
 };
 
 // A cluster's block step as the pool predictor fixed it: block size, block
@@ -498,8 +521,8 @@ struct PoolStatus {
 };
 
 // The small block steps that come next of every resident cluster, up to
-// kPoolTeamSteps, in their teams.
-hipError_t launch_pool_team(const PoolSlot* slots, const PoolTable* tab, bool mixed, hipStream_t s);
+// steps, in their teams.
+hipError_t launch_pool_team(const PoolSlot* slots, const PoolTable* tab, int steps, bool mixed, hipStream_t s);
 hipError_t launch_pool_step(const PoolSlot* slots, const PoolTable* tab, PoolWork* work, bool mixed,
                             hipStream_t s);
 // Lagrange radii of the ascending fractions frac[0..n_frac) into out[0..n_frac),
@@ -525,8 +548,8 @@ hipError_t launch_step_correct(const Dev& d, const Consts& c, int par, hipStream
 // The small block steps that come next, up to kTeamSteps, in one launch; ends
 // before a step of parity par, with its list prepared.
 hipError_t launch_team(const Dev& d, const Consts& c, const Team& t, int par, hipStream_t s);
-// Clears a team's exchange lines and its part of the schedule record.
-hipError_t launch_team_clear(const Dev& d, const Team& t, hipStream_t s);
+// Clears the exchange lines of a cluster of n particles and its part of the schedule record.
+hipError_t launch_team_clear(const Dev& d, int n, hipStream_t s);
 // Predicts every particle to the next block time and builds list 0 for it,
 // so that a step of parity 0 finds its list prepared.
 hipError_t launch_prepare(const Dev& d, const Consts& c, hipStream_t s);

@@ -2852,7 +2852,7 @@ __global__ __launch_bounds__(kBlock) void k_pool_predict(const PoolSlot* __restr
 // and none waits for another's larger step.
 template <bool kMixed>
 __global__ __launch_bounds__(kTeamBlock) void k_pool_team(const PoolSlot* __restrict__ slots,
-                                                          const PoolTable* __restrict__ tab) {
+                                                          const PoolTable* __restrict__ tab, int steps) {
   __shared__ int s_off[kMaxPool + 1];
   const int tid = threadIdx.x, count = tab->count;
   for (int k = tid; k <= kMaxPool; k += kTeamBlock) s_off[k] = tab->team_off[k];
@@ -2861,7 +2861,11 @@ __global__ __launch_bounds__(kTeamBlock) void k_pool_team(const PoolSlot* __rest
   const PoolItem it = pool_item(s_off, tab->order, nullptr, count, blockIdx.x);
   const PoolSlot& ps = slots[it.slot];
   const DevC d = compact_view(ps.d);
-  team_body<false, false, kMixed, false>(d, ps.c, ps.t, it.blk, kPoolTeamSteps, -1);
+  Team t = ps.t;
+  t.g = tab->team_g[it.k];
+  t.cap = tab->team_cap[it.k];
+  t.wgs = t.wp * t.g;
+  team_body<false, false, kMixed, false>(d, ps.c, t, it.blk, steps, -1);
 }
 
 template <bool kMixed>
@@ -3387,8 +3391,8 @@ hipError_t launch_team(const Dev& d, const Consts& c, const Team& t, int par, hi
   return hipGetLastError();
 }
 
-hipError_t launch_team_clear(const Dev& d, const Team& t, hipStream_t s) {
-  const size_t words = team_line_bytes(t) / 16;
+hipError_t launch_team_clear(const Dev& d, int n, hipStream_t s) {
+  const size_t words = team_room(n) / 16;
   hipLaunchKernelGGL(k_team_clear, dim3(grid_for((int)words) + 1), dim3(kBlock), 0, s, d.sc, (uint4*)d.xch,
                      (int)words);
   return hipGetLastError();
@@ -3520,9 +3524,9 @@ hipError_t launch_diagnostics(const Dev& d, const Consts& c, const double* frac,
   return hipGetLastError();
 }
 
-hipError_t launch_pool_team(const PoolSlot* slots, const PoolTable* tab, bool mixed, hipStream_t s) {
+hipError_t launch_pool_team(const PoolSlot* slots, const PoolTable* tab, int steps, bool mixed, hipStream_t s) {
   hipLaunchKernelGGL(mixed ? k_pool_team<true> : k_pool_team<false>, dim3(kPoolTeamWgs), dim3(kTeamBlock),
-                     sizeof(TeamMem), s, slots, tab);
+                     sizeof(TeamMem), s, slots, tab, steps);
   return hipGetLastError();
 }
 
