@@ -1995,7 +1995,8 @@ __device__ __forceinline__ void team_body(const DevC& d, const Consts& c, const 
       sc->clamps += s.clamp;
       if (s.bad) sc->nonfinite = 1;
       sc->team_epoch = epoch;
-      if (par >= 0) sc->spec = done ? -2 : (t_next << 1) | par;
+      // (after a non-finite sum the list is not built: the next step builds it)
+      if (par >= 0) sc->spec = done || s.bad ? -2 : (t_next << 1) | par;
     }
   }
 }
