@@ -100,7 +100,7 @@ struct Sched {
   Plan plan;                 // force decomposition of the step in flight
   int hist[kMaxLevels + 1];  // particles per level
   // Team kernel (k_team): workgroups that have started, and that have
-  // finished; launches to leave out.
+  // finished (kTeamOff: called off); launches to leave out.
   int team_join, team_vote, team_skip;
   unsigned team_epoch;  // steps published in the exchange lines since they were cleared
 };
@@ -213,6 +213,8 @@ constexpr int kTeamLine = 128;       // bytes of one exchange line (6 sums with 
 constexpr int kTeamPairs = 1 << 22;  // most pairs (n_act * n) of a team's step
 constexpr int kTeamSteps = 1024;     // most steps of one launch of a context's team
 constexpr unsigned kTeamLastEpoch = 0xFFFF0000u;
+constexpr int kTeamOff = 1 << 30;    // in team_join or team_vote: the launch is called off
+constexpr int kTeamSkip = 64;        // launches left out after one that did not find room
 
 // A team's workgroups share a cluster: workgroup w + wp * grp owns the j
 // slices w, w + width, ... (ks of them), of the one-particle decomposition's s1

@@ -703,6 +703,19 @@ __device__ __forceinline__ void finish_item(const Dev& d, const Consts& c, int L
   }
 }
 
+// What becomes of a cluster's team launch (k_team, k_pool_team), by one thread
+// of the kernel after it: a launch decides by these words and so writes none
+// of them before all of its workgroups have taken part.
+__device__ __forceinline__ void team_ended(Sched* __restrict__ sc) {
+  const int join = sc->team_join, vote = sc->team_vote, skip = sc->team_skip;
+  const unsigned epoch = sc->team_epoch;
+  sc->team_join = 0;
+  sc->team_vote = 0;
+  sc->team_skip = (join & kTeamOff) ? kTeamSkip : max(0, skip - 1);
+  // (no epoch that a workgroup may have published is used again)
+  sc->team_epoch = (vote & kTeamOff) ? epoch + kTeamSteps + 1u : epoch;
+}
+
 // kStep: the force kernel of a graph-replayed block step (k_step_force), with
 // the active list of parity par; otherwise that of a step whose predictor ran
 // before (list 0). kSrc: where the particles are read from (see ListArgs).
@@ -823,12 +836,7 @@ __device__ __forceinline__ void force_body(const Dev& d, const Consts& c, int bl
     const long long prepared =
         (long long)(((unsigned long long)(unsigned)__builtin_amdgcn_readfirstlane((int)(word >> 32)) << 32) |
                     (unsigned)__builtin_amdgcn_readfirstlane((int)word));
-    if (blk == 0 && tid == 0) {
-      // (the team kernel before this one has ended)
-      sc->team_join = 0;
-      sc->team_vote = 0;
-      sc->team_skip = max(0, sc->team_skip - 1);
-    }
+    if (blk == 0 && tid == 0) team_ended(sc);
     if (nx.done) {
       if (blk == 0 && tid == 0) {
         sc->done = 1;
@@ -1346,7 +1354,6 @@ __global__ __launch_bounds__(kBlock) void k_step_correct(DevC d, Consts c, int p
 // launch that was called off leaves its steps to the kernels that follow it.
 
 constexpr long long kJoinTicks = 3000;      // 30 us of the 100 MHz clock
-constexpr int kTeamSkip = 64;               // launches left out after one that did not find room
 constexpr long long kVoteTicks = 10000000;  // 100 ms
 constexpr int kStuckPolls = 1 << 16;    // of an exchange's lines: 10 ms and more
 constexpr int kTeamLevels = (kTeamMaxSlots * kTeamBlock + kTeamBlock * 16 - 1) / (kTeamBlock * 16);  // 16-byte loads of levels per thread
@@ -1364,7 +1371,6 @@ __device__ __forceinline__ void team_sync() {
 
 // Waits until all wgs workgroups have added themselves to *word (thread 0 of
 // each, after it has added its own), at most ticks: whether they have.
-constexpr int kTeamOff = 1 << 30;
 __device__ __forceinline__ bool team_agreed(int* word, int wgs, long long ticks) {
   const long long t0 = wall_clock64();
   for (;;) {
@@ -1654,13 +1660,13 @@ __device__ __forceinline__ void team_body(const DevC& d, const Consts& c, const 
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int n = c.n, kmax = c.kmax;
 
-  // Every workgroup decides alike: the record is not written before all of
-  // them have joined.
+  // Every wave of every workgroup decides alike: of what is read here, nothing
+  // is written before all workgroups have voted (and in a launch that is called
+  // off, nothing at all: see team_ended).
   const long long t_end = sc->t_end;
   const long long t_start = sc->t_now;
   long long t_now = t_start;
-  const unsigned epoch0 = sc->team_epoch;
-  unsigned epoch = epoch0;
+  unsigned epoch = sc->team_epoch;
   {
     const NextStep nx = schedule_wave(sc, c);
     if (nx.done || nx.n_act > t.cap || epoch >= kTeamLastEpoch || sc->nonfinite || sc->team_skip > 0) return;
@@ -1761,10 +1767,7 @@ __device__ __forceinline__ void team_body(const DevC& d, const Consts& c, const 
       s.go = t.wgs == 1 || team_agreed(&sc->team_join, t.wgs, kJoinTicks);
     }
     team_sync();
-    if (!s.go) {
-      if (me == 0 && tid == 0) sc->team_skip = kTeamSkip;
-      return;
-    }
+    if (!s.go) return;
     int at = incl - cnt;
 #pragma unroll
     for (int w = 0; w < kTeamWaves; ++w) at += w < wave ? s.wcnt[w] : 0;
@@ -1942,11 +1945,7 @@ __device__ __forceinline__ void team_body(const DevC& d, const Consts& c, const 
     }
   }
   team_sync();
-  if (!s.go) {
-    // (no epoch that a workgroup may have published is used again)
-    if (me == 0 && tid == 0) sc->team_epoch = epoch0 + (unsigned)max_steps + 1u;
-    return;
-  }
+  if (!s.go) return;
   // The corrected particles of the owned slices; the next step's list and j
   // stream; the record.
   if (o.grp == 0) {
@@ -2406,10 +2405,7 @@ __device__ __forceinline__ void predict_body(const Dev& d, const Consts& c, int 
         sc->done = done;
         if (nact > 0) sc->plan = pl;
         if (work) {
-          // (the teams of this round have ended)
-          sc->team_join = 0;
-          sc->team_vote = 0;
-          sc->team_skip = max(0, sc->team_skip - 1);
+          team_ended(sc);
           const bool w = !done && nact > 0;
           const int per_wg = w ? kBlock / correct_lanes(pl.s) : 1;
           work->force_n[k] = w ? pl.items : 0;
