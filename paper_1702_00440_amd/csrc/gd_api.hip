@@ -1077,7 +1077,7 @@ struct gd_pool {
   PoolTable* h_tab = nullptr;      // pinned staging
   PoolSlot* h_slot = nullptr;      // pinned staging
   double* h_e = nullptr;           // pinned energy result
-  bool staged = false;             // uploads from h_tab and h_slot may still run
+  bool stale = true;               // the device's table is not that of the resident clusters
   std::vector<PoolSlotHost> slots;
   std::string err;
 
@@ -1116,16 +1116,15 @@ bool pool_place(gd_pool* P, size_t bytes, size_t* off) {
   return true;
 }
 
-// Uploads the table of resident clusters (stream-ordered).
-// Waits for the stream.
+// Every call waits for its own work before it returns, so that nothing of a
+// pool's is under way in the arena or in the staging buffers between calls.
 gd_status pool_sync(gd_pool* P) {
-  GD_TRY(P->hip(hipStreamSynchronize(P->stream), "synchronise"));
-  P->staged = false;
-  return GD_OK;
+  return P->hip(hipStreamSynchronize(P->stream), "synchronise");
 }
 
+// Uploads the table of resident clusters (stream-ordered), for the replay that
+// the caller queues next.
 gd_status pool_upload_table(gd_pool* P) {
-  if (P->staged) GD_TRY(pool_sync(P));
   PoolTable& t = *P->h_tab;
   t.count = 0;
   int acc = 0, wgs = 0;
@@ -1156,9 +1155,10 @@ gd_status pool_upload_table(gd_pool* P) {
   t.pred_off[t.count] = acc;
   t.team_off[t.count] = wgs;
   P->round = !teams || wgs > kPoolTeamWgs ? 0 : g < kPoolWide ? 1 : 2;
-  P->staged = true;
-  return P->hip(hipMemcpyAsync(P->d_tab, P->h_tab, sizeof(PoolTable), hipMemcpyHostToDevice, P->stream),
-                "upload pool table");
+  GD_TRY(P->hip(hipMemcpyAsync(P->d_tab, P->h_tab, sizeof(PoolTable), hipMemcpyHostToDevice, P->stream),
+                "upload pool table"));
+  P->stale = false;
+  return GD_OK;
 }
 
 gd_status pool_energy(gd_pool* P, PoolSlotHost& s, double* e) {
@@ -1249,7 +1249,7 @@ gd_status gd_pool_create(gd_pool** out, const gd_params* p, int32_t max_clusters
   if (st == GD_OK) st = P->hip(hipHostMalloc((void**)&P->h_e, 4 * sizeof(double), 0), "pinned energy");
   if (st == GD_OK)
     st = P->hip(hipStreamCreateWithFlags(&P->capture_stream, hipStreamNonBlocking), "capture stream");
-  if (st == GD_OK) st = pool_upload_table(P);
+  if (st == GD_OK) st = pool_sync(P);
   if (st != GD_OK) {
     g_init_error = P->err;
     gd_pool_destroy(P);
@@ -1290,7 +1290,8 @@ gd_status gd_pool_admit(gd_pool* P, int64_t n, const double* m, const double* x,
   s.d = carve(P->arena + off, L);
   s.c = make_consts(&P->p, n, kmax, true);
   s.team = make_team((int)n, ipl_of(s.c), n1_of(s.c), true);
-  // Initialisation of the cluster (Sec. 2.4 steps 2-3) on the pool stream.
+  // Initialisation of the cluster (Sec. 2.4 steps 2-3) on the pool stream, and
+  // its descriptor (which nothing reads before the cluster is resident).
   auto undo = [&](gd_status st) {
     s = PoolSlotHost();
     return st;
@@ -1311,11 +1312,6 @@ gd_status gd_pool_admit(gd_pool* P, int64_t n, const double* m, const double* x,
   }
   if ((st = P->hip(launch_set_tend(s.d, s.t_end, P->stream), "prepare")) != GD_OK) return undo(st);
   if ((st = P->hip(launch_status_out(s.d.sc, P->h_sc, P->stream), "read status")) != GD_OK) return undo(st);
-  if ((st = pool_sync(P)) != GD_OK) return undo(st);
-  if (P->h_sc->bad_input) return undo(P->fail(GD_EINVAL, "non-finite or negative input (m, x or v)"));
-  if (P->h_sc->nonfinite) return undo(P->fail(GD_ENONFINITE, "non-finite initial acceleration or jerk"));
-  s.e0 = P->h_e[0] + P->h_e[1];
-  // Descriptor, then the table that makes the cluster resident.
   P->h_slot->d = s.d;
   P->h_slot->c = s.c;
   P->h_slot->t = s.team;
@@ -1323,8 +1319,12 @@ gd_status gd_pool_admit(gd_pool* P, int64_t n, const double* m, const double* x,
                                   P->stream),
                    "upload slot")) != GD_OK)
     return undo(st);
+  if ((st = pool_sync(P)) != GD_OK) return undo(st);
+  if (P->h_sc->bad_input) return undo(P->fail(GD_EINVAL, "non-finite or negative input (m, x or v)"));
+  if (P->h_sc->nonfinite) return undo(P->fail(GD_ENONFINITE, "non-finite initial acceleration or jerk"));
+  s.e0 = P->h_e[0] + P->h_e[1];
   s.resident = true;
-  if ((st = pool_upload_table(P)) != GD_OK) return undo(st);
+  P->stale = true;
   *slot_out = sl;
   return GD_OK;
 }
@@ -1335,10 +1335,12 @@ gd_status gd_pool_run(gd_pool* P, int32_t* finished, int32_t* n_finished) {
   int resident = 0;
   for (const auto& s : P->slots) resident += s.resident;
   if (resident == 0) return GD_OK;
-  GD_TRY(pool_build_graph(P, P->round));
-  GD_TRY(P->hip(hipGraphLaunch(P->graph[P->round], P->stream), "pool graph launch"));
-  GD_TRY(pool_sync(P));
-  bool changed = false;
+  if (P->stale) GD_TRY(pool_upload_table(P));
+  gd_status ran = pool_build_graph(P, P->round);
+  if (ran == GD_OK) ran = P->hip(hipGraphLaunch(P->graph[P->round], P->stream), "pool graph launch");
+  const gd_status waited = pool_sync(P);  // (also for the table, if there is no replay)
+  GD_TRY(ran);
+  GD_TRY(waited);
   for (int sl = 0; sl < P->max_clusters; ++sl) {
     PoolSlotHost& s = P->slots[sl];
     if (!s.resident) continue;
@@ -1348,12 +1350,11 @@ gd_status gd_pool_run(gd_pool* P, int32_t* finished, int32_t* n_finished) {
       s.resident = false;
       s.t_done = std::chrono::steady_clock::now();
       s.status = failed ? GD_ENONFINITE : GD_OK;
-      changed = true;
+      P->stale = true;
       if (finished) finished[*n_finished] = sl;
       ++*n_finished;
     }
   }
-  if (changed) GD_TRY(pool_upload_table(P));
   return GD_OK;
 }
 
@@ -1387,9 +1388,8 @@ gd_status gd_pool_release(gd_pool* P, int32_t sl) {
   if (!P || sl < 0 || sl >= P->max_clusters) return GD_EINVAL;
   PoolSlotHost& s = P->slots[sl];
   if (!s.used) return P->fail(GD_EINVAL, "slot holds no cluster");
-  const bool was_resident = s.resident;
+  if (s.resident) P->stale = true;
   s = PoolSlotHost();
-  if (was_resident) GD_TRY(pool_upload_table(P));
   return GD_OK;
 }
 
