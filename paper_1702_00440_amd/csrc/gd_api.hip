@@ -542,7 +542,8 @@ namespace {
 
 // Arguments of an index list's force. The kernel may write the outputs itself
 // if each particle has one slice, unless they overlap what other workgroups
-// still read (the reduction writes them after the force kernel).
+// still read (the reduction writes them after the force kernel), or none is
+// wanted (results are then not looked at for non-finite values either).
 ListArgs list_args(const int32_t* idx, int n_act, int64_t n, const Plan& plan, double* acc, double* jerk,
                    const double* m, const double* x, const double* v, int* bad) {
   ListArgs a{};
@@ -561,8 +562,8 @@ ListArgs list_args(const int32_t* idx, int n_act, int64_t n, const Plan& plan, d
     };
     return clear(acc) && clear(jerk);
   };
-  a.direct = plan.s == 1 && apart(idx, 4 * (size_t)n_act) && apart(m, 8 * (size_t)n) && apart(x, 24 * (size_t)n) &&
-             apart(v, 24 * (size_t)n);
+  a.direct = plan.s == 1 && (acc || jerk) && apart(idx, 4 * (size_t)n_act) && apart(m, 8 * (size_t)n) &&
+             apart(x, 24 * (size_t)n) && apart(v, 24 * (size_t)n);
   return a;
 }
 
