@@ -424,6 +424,7 @@ gd_status gd_init(gd_ctx** out, const gd_params* p, int64_t n, const double* m, 
   c->team = make_team((int)n, ipl_of(c->c), n1_of(c->c), false);
   c->stream = (hipStream_t)hip_stream;
   c->d = carve(workspace, L);
+  if (!c->team.wgs) c->d.xch = nullptr;
   Dev& d = c->d;
 
   auto cleanup_fail = [&](gd_status st) {

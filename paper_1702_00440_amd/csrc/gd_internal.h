@@ -271,7 +271,7 @@ struct Dev {
   double* part;                            // [6][partial_rows(n)]: position * s + slot
   double* ebuf;                            // energy partials [grid][3]; results of the diagnostics
   int* nact_log;                           // force-timing pass: N_act of each timed step
-  char* xch;                               // a team's exchange lines
+  char* xch;                               // a team's exchange lines (null: a context without one)
 };
 
 // One force evaluation of an index list (gd_force with indices,
