@@ -29,6 +29,17 @@ namespace {
 
 constexpr int kGraphSteps = 64;  // block steps per captured graph
 constexpr int kTeamRounds = 16;  // per captured graph of a context with a team: a team launch and a block step
+// Of one without the team's launches (64: the empty steps at the end of a chunk
+// take more, N = 8192 with softening 0.05 11.5 instead of 11.4 ms).
+constexpr int kAloneSteps = 32;
+constexpr int kTeamBack = 32;    // most replays without the team after a launch that found no room
+// What a team's steps are worth against the two kernels (team_pays), in units of
+// what the smallest save: less for each active particle (at least), for each
+// pair, and what a step that is too large costs.
+constexpr double kTeamPerI = 0.0103, kTeamPerPair = 1.53e-6;
+constexpr double kTeamPerLarge = 2.2, kTeamPerLargeSmall = 1.3;  // (from kTeamLargeN particles on, below)
+constexpr int kTeamLargeN = 4096;
+constexpr double kTeamMemory = 0.875;  // weight of the replays before, from one to the next
 constexpr int kSchedWords = (int)((sizeof(Sched) + 7) / 8);  // 8-byte words of a status copy
 // Force-timing buckets by N_act: lower edges (the last bucket is open).
 constexpr int kProfBuckets = GD_PROFILE_BUCKETS;
@@ -212,6 +223,16 @@ Consts make_consts(const gd_params* p, int64_t n, int kmax, bool pool) {
 
 }  // namespace
 
+// Whether the replays of a context go with its team's launches, as the
+// schedule records before and after each replay tell: see choose_replay.
+struct TeamUse {
+  bool pays = true;      // the steps are such that it helps
+  double worth = 0.0;    // what its steps were worth, and how many were too large
+  double larger = 0.0;   // for it: of the last replays (team_pays)
+  int out = 0;           // replays that go without it because there was no room
+  int back = 2;          // the same after the next launch that finds none
+};
+
 struct gd_ctx {
   gd_params p{};
   long long n = 0;
@@ -223,8 +244,10 @@ struct gd_ctx {
   // Two instances of the captured block steps, each ending with a copy of the
   // schedule record into its own pinned buffer (h_ring[0] / h_ring[1]), with
   // an event recorded after each launch: replays can then be queued ahead of
-  // the host reading an earlier replay's status.
-  hipGraphExec_t graph[2] = {nullptr, nullptr};
+  // the host reading an earlier replay's status. Of each kind (see TeamUse):
+  // without the team's launches, and with them.
+  hipGraphExec_t graph[2][2] = {};
+  TeamUse use;
   Sched* h_ring[2] = {nullptr, nullptr};
   hipEvent_t ev_ring[2] = {nullptr, nullptr};
   bool prof = false, ev_ready = false;
@@ -326,18 +349,18 @@ gd_status enqueue_step(gd_ctx* c, hipStream_t s, int par, hipEvent_t ev_s, hipEv
   return c->hip(launch_step_correct(c->d, c->c, par, s), "correct kernel");
 }
 
-// Captures kGraphSteps block steps into *out.
-gd_status build_graph(gd_ctx* c, int ring) {
-  hipGraphExec_t* out = &c->graph[ring];
+// Captures the block steps of one replay, with the team's launches or without.
+gd_status build_graph(gd_ctx* c, bool team, int ring) {
+  hipGraphExec_t* out = &c->graph[team][ring];
   if (*out) return GD_OK;
   hipGraph_t g = nullptr;
   GD_TRY(c->hip(hipStreamBeginCapture(c->capture_stream, hipStreamCaptureModeThreadLocal),
                 "begin capture"));
   gd_status st = GD_OK;
   // With a team: the small steps that come next, then a step of any size.
-  const int rounds = c->team.wgs ? kTeamRounds : kGraphSteps;
+  const int rounds = team ? kTeamRounds : c->team.wgs ? kAloneSteps : kGraphSteps;
   for (int k = 0; k < rounds && st == GD_OK; ++k) {
-    if (c->team.wgs) st = c->hip(launch_team(c->d, c->c, c->team, k & 1, c->capture_stream), "team kernel");
+    if (team) st = c->hip(launch_team(c->d, c->c, c->team, k & 1, c->capture_stream), "team kernel");
     if (st == GD_OK) st = enqueue_step(c, c->capture_stream, k & 1, nullptr, nullptr);
   }
   if (st == GD_OK) st = c->hip(launch_status_out(c->d.sc, c->h_ring[ring], c->capture_stream), "status kernel");
@@ -385,6 +408,7 @@ gd_status initialise(gd_ctx* c, const double* m, const double* x, const double* 
   c->e0 = c->e_last = c->h_e[0] + c->h_e[1];
   c->t_now = 0;
   c->wall_s = 0.0;
+  c->use = TeamUse();
   c->synced = true;
   c->phase = kIdle;
   return GD_OK;
@@ -662,6 +686,54 @@ gd_status gd_correct(gd_ctx* c) {
 
 namespace {
 
+// Whether steps like those between two records (and, with less weight, those of
+// the replays before) are such that a team helps. Against the two kernels it
+// saves 5 to 9 us a step, less 0.05 us for each active particle or (above N =
+// 6700) 7 us for each 10^6 pairs, since a part of the chip computes them; and a
+// step that is too large for it costs 12 us: the launch before it, joining,
+// reading the set. Fitted to integrations of spheres of N = 600 to 32512 with
+// softenings of 1e-4 to 0.05. Half a time unit of N = 8192, softening 0.02, with
+// as many large blocks as small: 22.9 ms without the team, 26.0 with it in every
+// replay, 22.7 by this rule; an eighth of N = 16384, softening 1e-4: 58.9, 51.5
+// and 51.7.
+bool team_pays(const gd_ctx* c, TeamUse& u, const Sched& before, const Sched& after) {
+  // (the bins that lie below the team's largest step as a whole)
+  const int bins = c->team.cap >= c->n ? kNactBins : 31 - __builtin_clz((unsigned)c->team.cap + 1u);
+  const double per = std::max(kTeamPerI, kTeamPerPair * (double)c->n);
+  long long sized = 0;
+  double worth = 0.0;
+  for (int b = 0; b < bins; ++b) {
+    const long long k = after.nact_hist[b] - before.nact_hist[b];
+    sized += k;
+    worth += (double)k * (1.0 - per * (double)(1LL << b));
+  }
+  u.worth = u.worth * kTeamMemory + worth;
+  u.larger = u.larger * kTeamMemory + (double)(after.block_steps - before.block_steps - sized);
+  return u.worth >= (c->n < kTeamLargeN ? kTeamPerLargeSmall : kTeamPerLarge) * u.larger;
+}
+
+// Whether the replays after this one go with the team, from the records before
+// and after a replay that did (teamed) or did not.
+//   - After a launch that found no room: without it for back replays, twice as
+//     many each time (up to kTeamBack) until one finds room again. (A replay
+//     without it takes as many steps as there are launches left out.) Three
+//     contexts of N = 16384 on streams of their own, an eighth of a time unit:
+//     98.1 ms without teams, 100.2 with, 96.8 this way.
+//   - While it does not pay. A replay that ended its chunk does not decide: the
+//     shorter replays with the team leave fewer empty steps there.
+void choose_replay(gd_ctx* c, bool teamed, const Sched& before, const Sched& after, bool ended) {
+  TeamUse& u = c->use;
+  if (teamed && after.team_skip > 0) {
+    u.out = u.back;
+    u.back = std::min(2 * u.back, kTeamBack);
+  } else if (teamed) {
+    u.back = TeamUse().back;
+  } else if (u.out > 0) {
+    --u.out;
+  }
+  if (!ended) u.pays = team_pays(c, u, before, after);
+}
+
 // Graph replays until the schedule reaches chunk_end; on return h_sc holds
 // the status after the last replay that did work. The next replay is queued
 // before the host reads the previous one's status, so that the device does
@@ -671,9 +743,12 @@ namespace {
 // device skips every step past it.
 gd_status replay_chunk(gd_ctx* c, long long chunk_end) {
   int next = 0, head = 0, inflight = 0;
+  bool teamed[2] = {};
   long long t_prev = c->t_now, adv = 0;
   auto queue = [&]() -> gd_status {
-    GD_TRY(c->hip(hipGraphLaunch(c->graph[next], c->stream), "graph launch"));
+    const bool team = teamed[next] = c->team.wgs && c->use.pays && c->use.out == 0;
+    GD_TRY(build_graph(c, team, next));
+    GD_TRY(c->hip(hipGraphLaunch(c->graph[team][next], c->stream), "graph launch"));
     GD_TRY(c->hip(hipEventRecord(c->ev_ring[next], c->stream), "status event"));
     next ^= 1;
     ++inflight;
@@ -683,6 +758,8 @@ gd_status replay_chunk(gd_ctx* c, long long chunk_end) {
   for (;;) {
     if (inflight == 1 && adv > 0 && chunk_end - t_prev > 2 * adv) GD_TRY(queue());
     GD_TRY(c->hip(hipEventSynchronize(c->ev_ring[head]), "status wait"));
+    if (c->team.wgs)
+      choose_replay(c, teamed[head], *c->h_sc, *c->h_ring[head], c->h_ring[head]->t_now >= chunk_end);
     *c->h_sc = *c->h_ring[head];
     head ^= 1;
     --inflight;
@@ -716,11 +793,8 @@ gd_status gd_step_to(gd_ctx* c, double t_end, gd_stats* st) {
   const long long target = (long long)q * per_max;
   if (target < c->t_now) return c->fail(GD_EINVAL, "t_end is before the current time");
   // Profiling runs the same steps as direct launches (the force launches
-  // carry timing events); otherwise a captured graph is replayed.
-  if (!c->prof) {
-    GD_TRY(build_graph(c, 0));
-    GD_TRY(build_graph(c, 1));
-  }
+  // carry timing events); otherwise a captured graph is replayed (captured
+  // when it is first queued).
   c->phase = kIdle;
   c->prog_t0 = c->prog_last = std::chrono::steady_clock::now();
   c->prog_target = t_end;
@@ -867,6 +941,7 @@ gd_status gd_set_state(gd_ctx* c, const double* x, const double* v, const double
   if (c->h_sc->bad_input) return c->fail(GD_EINVAL, "invalid state (times, steps or non-finite values)");
   c->t_now = tn;
   c->wall_s = 0.0;
+  c->use = TeamUse();
   c->phase = kIdle;
   // Synchronised only when every particle sits at t_now.
   c->synced = (tn % (1LL << c->c.kmax)) == 0;
@@ -908,7 +983,8 @@ gd_status gd_stats_get(gd_ctx* c, gd_stats* st) {
 void gd_destroy(gd_ctx* c) {
   if (!c) return;
   for (int r = 0; r < 2; ++r) {
-    if (c->graph[r]) (void)hipGraphExecDestroy(c->graph[r]);
+    for (int team = 0; team < 2; ++team)
+      if (c->graph[team][r]) (void)hipGraphExecDestroy(c->graph[team][r]);
     if (c->ev_ring[r]) (void)hipEventDestroy(c->ev_ring[r]);
     if (c->h_ring[r]) (void)hipHostFree(c->h_ring[r]);
   }
