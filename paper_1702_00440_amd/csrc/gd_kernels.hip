@@ -3139,9 +3139,11 @@ __device__ __forceinline__ double diag_block_scan(double v, double* part, double
 //
 // The definition is in sums taken one after the other (total mass in index
 // order, cumulative mass in sorted order), a serial chain. Prefix sums of the
-// whole workgroup decide the same wherever they can: any order of adding n
-// masses >= 0 is off by at most (n - 1) 2^-53 of the total, so a threshold
-// further than delta from the cumulative masses on both its sides is crossed
+// whole workgroup decide the same wherever they can: adding n masses >= 0 one
+// after the other is off by at most (n - 1) 2^-53 of the total, for the threshold
+// and for the cumulative mass, and the sums here by their chains, 8 + n / 256
+// (the total) and 26 + n / 4096; so a threshold further than delta (all of
+// them, and more) from the cumulative masses on both its sides is crossed
 // at the same particle; and when every mass is a multiple of the spacing of
 // doubles at the total (equal masses 1 / 2^k), all orders are exact. A
 // threshold that neither settles (equal masses 1 / 1000 at f = 1/2) takes the
@@ -3164,7 +3166,7 @@ __global__ __launch_bounds__(kDiagScanBlock) void k_diag_scan(int n, int nwg, co
   double tot[4];
   diag_totals(wg, nwg, stage, tot);
   double mt = tot[0];
-  const double delta = (2.0 * n + 256.0) * 0x1p-53 * mt;
+  const double delta = (2.01 * n + 256.0) * 0x1p-53 * mt;
   // spacing of doubles at twice the total: multiples of it add exactly
   int e;
   (void)frexp(2.0 * mt, &e);
