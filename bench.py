@@ -19,10 +19,12 @@ The force kernel's per-launch durations come from HIP events that record
 each launch's own start and end (hipExtLaunchKernelGGL) during one more
 integration of the same workload right after the timed steps; in that pass
 the steps are launched directly rather than replayed from a graph (events
-recorded by a captured graph cannot be timed). The kernels are the same, but
-one launched from an idle GPU runs about a fifth longer than inside a replay
-(rocprofv3), so the fraction reported is the lower reading. The same pass
-splits the launches by block size (force_by_n_act), and the roofline line
+recorded by a captured graph cannot be timed). In that pass the force kernel
+takes every block step; in the timed steps a team of resident workgroups takes
+most of the small ones (up to 256 active particles), and the force kernel the
+rest. One launched from an idle GPU runs about a fifth longer than inside a
+replay (rocprofv3), so the fraction reported is the lower reading. The same
+pass splits the launches by block size (force_by_n_act), and the roofline line
 also gives the fraction reached by the launches with N_act >= 4096.
 """
 import argparse

@@ -134,10 +134,13 @@ gd_status gd_reinit(gd_ctx* c, const double* m, const double* x, const double* v
  * every force launch issued by gd_reinit, gd_step_to and gd_force with an
  * index list records its own start and end in HIP events
  * (hipExtLaunchKernelGGL); the elapsed times of
- * the launches that did work are summed. Counters restart at zero on every
- * call. gd_profile_get reports the summed milliseconds, the number of such
- * launches, and their pair interactions (N_act * N each). Host outputs; any
- * may be NULL. Results are identical with and without timing.
+ * the launches that did work are summed. (The initial force of 32768 particles
+ * and more, in FP64 without a central particle, is several launches: timed from
+ * the start of the first to the end of the last, counted as one.) Counters
+ * restart at zero on every call. gd_profile_get reports the summed
+ * milliseconds, the number of such launches, and their pair interactions
+ * (N_act * N each). Host outputs; any may be NULL. Results are identical with
+ * and without timing.
  * Errors: GD_EINVAL for a NULL context; GD_EHIP (event creation).
  */
 gd_status gd_profile_force(gd_ctx* c, int enable);

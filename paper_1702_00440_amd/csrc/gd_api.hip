@@ -27,7 +27,7 @@ using namespace gd;
 
 namespace {
 
-constexpr int kGraphSteps = 64;  // block steps per captured graph
+constexpr int kGraphSteps = 64;  // block steps per captured graph of a context without a team, and per timed batch
 constexpr int kTeamRounds = 16;  // per captured graph of a context with a team: a team launch and a block step
 // Of one without the team's launches (64: the empty steps at the end of a chunk
 // take more, N = 8192 with softening 0.05 11.5 instead of 11.4 ms).
@@ -101,8 +101,9 @@ Layout make_layout(long long n, int ipl) {
   L.part = take(sizeof(double) * 6 * (size_t)partial_rows(n, ipl));
   L.ebuf = take(sizeof(double) * 3 * kEnergyGrid);
   L.nact_log = take(sizeof(int) * 72);
-  // (contexts of a size that has teams hold kIPerLane i per lane; a pool's
-  // team of the same cluster has fewer owners and groups)
+  // (contexts of a size that has teams hold kIPerLane i per lane; a pool's team
+  // of the same cluster can have more owners or groups, and pool_team ends its
+  // largest step where its lines would not fit)
   L.xch = take(team_room((int)n));
   L.total = off;
   return L;
@@ -1106,18 +1107,19 @@ gd_status gd_force_noalloc(const gd_params* p, int64_t n, const double* m, const
 // ===========================================================================
 //
 // A pool owns one caller-provided arena: the device tables (slot descriptors,
-// the table of resident clusters, the status array), then the clusters'
+// the table of resident clusters, the work of a pool step), then the clusters'
 // workspaces, placed first-fit as clusters are admitted and freed as they
 // are released. Admission is by footprint: a cluster is admitted when a slot
-// and a gap of gd_workspace_bytes(n) bytes are free. One call of
-// gd_pool_run replays a captured graph of kPoolSteps pool steps; each pool
-// step advances every resident cluster by one of its own block steps, with
-// one launch per phase for all of them. Clusters that reach their end time
-// stop (their steps become no-ops) and are reported.
+// and a gap of gd_workspace_bytes(n) bytes are free. One call of gd_pool_run
+// replays a captured graph of up to kPoolSteps block steps of every resident
+// cluster: pool steps, each of one block step of every cluster with one launch
+// per phase for all of them, and between them (kPoolTeamSteps) the small block
+// steps in teams. Clusters that reach their end time stop (their steps become
+// no-ops) and are reported.
 
 namespace {
 
-constexpr int kPoolSteps = 32;  // pool steps per captured graph
+constexpr int kPoolSteps = 32;  // block steps of a cluster per captured graph
 
 // Teams with few steps to a round (kPoolTeamSteps) have to take the clusters
 // on by kPoolPays steps a round on average, over the last runs; below that, the

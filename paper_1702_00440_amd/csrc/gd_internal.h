@@ -9,7 +9,8 @@
 
 namespace gd {
 
-// Launch geometry. Every kernel runs 256-lane workgroups (4 wave64s).
+// Launch geometry. Workgroups have 256 lanes (4 wave64s), except those of the
+// teams and of k_sym_force (512), and of the diagnostics' sort (512) and scan (1024).
 constexpr int kBlock = 256;
 // j particles staged per LDS tile.
 constexpr int kTileJ = 256;
@@ -74,10 +75,11 @@ struct Plan {
 // Device-resident scheduling and bookkeeping record (lives in the workspace).
 //
 // Block steps replayed from a graph run two kernels each (k_step_force,
-// k_step_correct; small ones in a team, see k_team), and the step's parity (0/1, a kernel argument) picks one of
-// two active lists: the corrector of a step predicts every particle to the
-// speculated next block time and builds the next step's list in the other
-// list, and the next force kernel checks the speculation (see k_step_force).
+// k_step_correct; small ones in a team, see k_team), and the step's parity
+// (0/1, a kernel argument) picks one of two active lists: the corrector of a
+// step predicts every particle to the speculated next block time and builds
+// the next step's list in the other list, and the next force kernel checks the
+// speculation (see k_step_force).
 struct Sched {
   long long t_now;   // current block time, in dt_min ticks
   long long t_next;  // block time of the step in flight

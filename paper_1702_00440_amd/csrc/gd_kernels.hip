@@ -388,8 +388,8 @@ __device__ __forceinline__ int wg_append(bool take, int* counter) {
   return pos;
 }
 
-// k_step_correct's (and k_team's) view of a context's arrays: the first array of each group
-// that the workspace layout places one stride apart (the state x .. jz, the j
+// k_step_correct's (and k_team's) view of a context's arrays: the first array of
+// each group that the workspace layout places one stride apart (the state x .. jz, the j
 // stream px .. pvz, the list arrays ix .. ijz), with the two strides. Array k
 // of a group is addressed where it is used (st_arr, pj_arr, il_arr). Passing
 // the 41 pointers of Dev, or computing them all when the kernel starts, left
@@ -1295,8 +1295,9 @@ __global__ __launch_bounds__(kBlock) void k_step_correct(DevC d, Consts c, int p
 // Three quarters of the steps have a few active particles. Two kernels per
 // step then take 8 us (N = 1024) to 12.5 us (N = 16384) for under 1 us of
 // pairs: launch boundaries, and a chain of dependent memory round trips in
-// each kernel. A team of up to 32 workgroups takes such steps one after the
-// other without a launch between them:
+// each kernel. A team of up to 128 workgroups (make_team; in a pool up to 256 for
+// all teams together) takes such steps one after the other without a launch
+// between them:
 //   - every workgroup keeps the schedule (clock, level histogram), the set of
 //     the finest particles (all those of a level of at least `floor`, at most
 //     cap of them) with their state in LDS, and the state of the other j it
@@ -1689,8 +1690,9 @@ __device__ __forceinline__ void team_body(const DevC& d, const Consts& c, const 
   const long long sn = d.sn;
 
   // The owned j of this thread: places tid and, with more than two tiles, tid +
-  // 512; place p is in tile p / 256 of the owned slices', one after the other. Their state as the launch finds it: those of the set
-  // change, and are then read from the set (mem: their entries).
+  // 512; place p is in tile p / 256 of the owned slices', one after the other.
+  // Their state as the launch finds it: those of the set change, and are then
+  // read from the set (mem: their entries).
   constexpr int kOwn = kWhole ? kTeamTiles * kTileJ / kTeamBlock : 1;
   const int owns = t.ks * o.tps > kTeamBlock / kTileJ ? kOwn : 1;
   int j[kOwn], mem[kOwn];
@@ -1716,7 +1718,8 @@ __device__ __forceinline__ void team_body(const DevC& d, const Consts& c, const 
     s.clamp = 0;
     s.bad = 0;
     s.stuck = 0;
-    // the list that is prepared at the end is built anew
+    // The list that is prepared at the end is built anew. (Other workgroups count
+    // in it after the vote; this thread's next wait for a load is one for the store.)
     if (me == 0 && par >= 0) __hip_atomic_store(&sc->lcnt[par], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
 
